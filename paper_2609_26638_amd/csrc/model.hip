@@ -13,8 +13,8 @@
 // out [out, in] so both MFMA operands are contiguous along k.  K is cut into
 // a fixed number of logical splits that depends on K only; each output is the
 // in-order sum of the splits' in-order MFMA accumulations, whichever kernel
-// computes it (gemm_ws_kernel for calls of up to 256 rows, gemm_rt_kernel for
-// longer ones).  A row's result therefore never depends on how many rows the
+// computes it (gemm_ws_kernel and its kin for calls of up to 256 rows,
+// gemm_tile_kernel for longer ones).  A row's result therefore never depends on how many rows the
 // call carries, so an AR call (1 row) and a fused call (2B rows) produce
 // bit-identical rows.
 #include <algorithm>
@@ -452,9 +452,10 @@ __global__ void __launch_bounds__(256) gemm_bf16_kernel(const __bf16* __restrict
 //     (row tile x 32 columns) tile straight from global memory and the four
 //     splits are added through LDS in order -- no partials leave the
 //     workgroup;
-//   * gemm_rt_kernel (longer calls: prefill, wide multi-draft windows): LDS-
-//     staged tiles of MT rows x 128 columns, the splits' products added to a
-//     running sum in registers.
+//   * gemm_tile_kernel (gemm_tile.h; longer calls -- prefill, large batches,
+//     wide multi-draft windows -- and any call whose K has one split):
+//     LDS-staged tiles, each split's products added to a running sum in
+//     registers.
 // ---------------------------------------------------------------------------
 constexpr int GK_SPLITS = 4;        // logical K splits when K % 256 == 0
 constexpr int WS_MAX_ROWS = 256;    // calls up to this many rows use gemm_ws_kernel
@@ -513,6 +514,7 @@ struct GemmArgs {
   // rope_tab[row * rope_D / 2 + i] (rope_table_kernel)
   const double2* rope_tab;
   int rope_D;
+  int ksplit;        // logical K splits (gemm_ksplit)
 };
 
 __device__ __forceinline__ uint64_t pack_logit(float v, int idx, bool& nonfinite) {
@@ -1260,223 +1262,9 @@ __global__ void __launch_bounds__(256) argmax_rows_kernel(const uint64_t* __rest
   }
 }
 
-// ---------------------------------------------------------------------------
-// gemm_rt_kernel<MT>: C[M, N] = A[M, K] W[N, K]^T for long calls, tiles of MT
-// rows x 128 columns staged through LDS; all KS splits of a tile in one
-// workgroup, each split's product added to a running sum in registers.
-//
-// Waves: MT = 32 -> 1 x 4 (each wave 32 rows x 32 columns); MT >= 64 ->
-// 2 x 2 (each wave MT/2 rows x 64 columns).  Per 64-wide K chunk all 256
-// threads copy the A tile (MT x 64) and the W tile (128 x 64) into a
-// double-buffered LDS pair (16-byte chunks XOR-swizzled by row so the MFMA
-// operand reads are conflict-free); the global loads of the next P - 1
-// chunks are in flight while the current chunk is multiplied.
-// ---------------------------------------------------------------------------
-constexpr int RT_NT = 128;   // columns per tile
-constexpr int RT_KC = 64;    // K per LDS chunk
-
-// SPLITS = false: one logical split only (KS == 1), no running sum kept.
-template <int MT, bool SPLITS>
-__global__ void __launch_bounds__(256, 1) gemm_rt_kernel(
-    const __bf16* __restrict__ A, const __bf16* __restrict__ W, int M, int N, int K, void* C,
-    int c_f32, int accumulate, int KS, uint64_t* __restrict__ part, int32_t* err) {
-  constexpr bool WIDE = MT >= 64;
-  constexpr int RG = WIDE ? MT / 64 : 1;   // 32-row groups per wave
-  constexpr int CG = WIDE ? 2 : 1;         // 32-column groups per wave
-  constexpr int A_LD = MT * RT_KC / 8 / 256;      // 16-byte A chunks per thread per K chunk
-  constexpr int W_LD = RT_NT * RT_KC / 8 / 256;   // 16-byte W chunks per thread per K chunk
-  static_assert(A_LD >= 1 && W_LD >= 1, "tile / threads");
-  __shared__ __attribute__((aligned(16))) char s_a[2][MT * RT_KC * 2];
-  __shared__ __attribute__((aligned(16))) char s_w[2][RT_NT * RT_KC * 2];
-
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int l32 = lane & 31, hh = lane >> 5;
-  const int NBK = (N + RT_NT - 1) / RT_NT;
-  const int nb = blockIdx.x % NBK;
-  const int rt = blockIdx.x / NBK;
-  const int n0 = nb * RT_NT;
-  const int m0 = rt * MT;
-  const int kc = K / KS;
-  const int wr = WIDE ? (w >> 1) : 0, wc = WIDE ? (w & 1) : w;
-  const int row_w = wr * (MT / (WIDE ? 2 : 1));   // first tile row of the wave
-  const int col_w = wc * (CG * 32);               // first tile column of the wave
-
-  // global -> register staging of K chunks, P - 1 chunks ahead of the one
-  // being multiplied (ring slot = chunk index mod P)
-  constexpr int P = MT <= 64 ? 4 : 2;
-  u32x4 ra[P][A_LD], rw[P][W_LD];
-  auto load_chunk = [&](int k0, u32x4 (&xa)[A_LD], u32x4 (&xw)[W_LD]) {
-#pragma unroll
-    for (int j = 0; j < A_LD; ++j) {
-      const int idx = tid + j * 256;
-      const int r = idx >> 3, c = idx & 7;
-      // unconditional loads (rows past the end re-read the last row and are
-      // zeroed after), so that the wait counts stay exact across the ring
-      const int mrow = m0 + r;
-      const u32x4 x = *(const u32x4*)(A + (size_t)min(mrow, M - 1) * K + k0 + c * 8);
-      xa[j] = mrow < M ? x : u32x4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int j = 0; j < W_LD; ++j) {
-      const int idx = tid + j * 256;
-      const int r = idx >> 3, c = idx & 7;
-      const int n = n0 + r;
-      const u32x4 x = *(const u32x4*)(W + (size_t)min(n, N - 1) * K + k0 + c * 8);
-      xw[j] = n < N ? x : u32x4{0, 0, 0, 0};
-    }
-  };
-  auto store_chunk = [&](int buf, const u32x4 (&xa)[A_LD], const u32x4 (&xw)[W_LD]) {
-#pragma unroll
-    for (int j = 0; j < A_LD; ++j) {
-      const int idx = tid + j * 256;
-      const int r = idx >> 3, c = idx & 7;
-      *(u32x4*)(s_a[buf] + r * 128 + ((c ^ (r & 7)) << 4)) = xa[j];
-    }
-#pragma unroll
-    for (int j = 0; j < W_LD; ++j) {
-      const int idx = tid + j * 256;
-      const int r = idx >> 3, c = idx & 7;
-      *(u32x4*)(s_w[buf] + r * 128 + ((c ^ (r & 7)) << 4)) = xw[j];
-    }
-  };
-
-  f32x16 acc[RG][CG], sum[SPLITS ? RG : 1][SPLITS ? CG : 1];
-  if constexpr (SPLITS) {
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-      for (int b = 0; b < CG; ++b) sum[a][b] = f32x16{};
-  }
-
-  const int nch = kc / RT_KC;
-  const int total = KS * nch;
-  auto chunk_k0 = [&](int t) { return (t / nch) * kc + (t % nch) * RT_KC; };
-  static_for<0, P - 1>([&](auto c) {
-    constexpr int i = decltype(c)::value;
-    load_chunk(chunk_k0(min(i, total - 1)), ra[i], rw[i]);
-  });
-  store_chunk(0, ra[0], rw[0]);
-  __syncthreads();
-  // one chunk: acc reset at a split start, the next-but-(P-2) chunk's loads
-  // (clamped to the last chunk: a harmless re-read), the products, the
-  // ordered split sum, the next chunk into the other LDS buffer
-  auto step = [&](int t, auto cs) {
-    constexpr int sl = decltype(cs)::value;   // ring slot of chunk t
-    const int ch = t % nch;
-    if (ch == 0) {
-#pragma unroll
-      for (int a = 0; a < RG; ++a)
-#pragma unroll
-        for (int b = 0; b < CG; ++b) acc[a][b] = f32x16{};
-    }
-    load_chunk(chunk_k0(min(t + P - 1, total - 1)), ra[(sl + P - 1) % P], rw[(sl + P - 1) % P]);
-    const char* sa = s_a[t & 1];
-    const char* sw = s_w[t & 1];
-#pragma unroll
-    for (int ks = 0; ks < RT_KC / 16; ++ks) {
-      const int ch16 = ks * 2 + hh;   // 16-byte chunk of the row holding this lane's 8 k values
-      bf16x8 af[RG], bf[CG];
-#pragma unroll
-      for (int a = 0; a < RG; ++a) {
-        const int r = row_w + a * 32 + l32;
-        af[a] = *(const bf16x8*)(sa + r * 128 + ((ch16 ^ (r & 7)) << 4));
-      }
-#pragma unroll
-      for (int b = 0; b < CG; ++b) {
-        const int r = col_w + b * 32 + l32;
-        bf[b] = *(const bf16x8*)(sw + r * 128 + ((ch16 ^ (r & 7)) << 4));
-      }
-#pragma unroll
-      for (int a = 0; a < RG; ++a)
-#pragma unroll
-        for (int b = 0; b < CG; ++b)
-          acc[a][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[a], bf[b], acc[a][b], 0, 0, 0);
-    }
-    if (SPLITS && ch == nch - 1) {   // split complete: ordered running sum
-#pragma unroll
-      for (int a = 0; a < RG; ++a)
-#pragma unroll
-        for (int b = 0; b < CG; ++b) sum[a][b] += acc[a][b];
-    }
-    store_chunk((t + 1) & 1, ra[(sl + 1) % P], rw[(sl + 1) % P]);
-    __syncthreads();
-  };
-  // whole groups of P chunks keep the ring slots compile-time; the tail runs
-  // the same steps one by one
-  int t0 = 0;
-  for (; t0 + P <= total; t0 += P) static_for<0, P>([&](auto c) { step(t0 + decltype(c)::value, c); });
-  static_for<0, P - 1>([&](auto c) {
-    if (t0 + decltype(c)::value < total) step(t0 + decltype(c)::value, c);
-  });
-
-  // element (a, b, i) of this lane: row m0 + row_w + 32a + 8(i>>2) + 4hh + (i&3),
-  // column n0 + col_w + 32b + l32
-  float* Cf = c_f32 ? (float*)C : nullptr;
-  __bf16* Cb = c_f32 ? nullptr : (__bf16*)C;
-  auto write_out = [&](f32x16 (&v)[RG][CG]) {
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-      for (int b = 0; b < CG; ++b) {
-        const int n = n0 + col_w + b * 32 + l32;
-        float cur[16];
-        if (Cf && accumulate) {
-#pragma unroll
-          for (int i = 0; i < 16; ++i) {
-            const int mrow = m0 + row_w + a * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
-            cur[i] = (mrow < M && n < N) ? Cf[(size_t)mrow * N + n] : 0.f;
-          }
-        }
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int mrow = m0 + row_w + a * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
-          if (mrow >= M || n >= N) continue;
-          const size_t o = (size_t)mrow * N + n;
-          if (Cf) Cf[o] = accumulate ? cur[i] + v[a][b][i] : v[a][b][i];
-          else Cb[o] = (__bf16)v[a][b][i];
-        }
-      }
-  };
-  // top-1 epilogue (part != NULL): per row and 32-column group the largest
-  // value and its lowest index, packed as gemm_ws_kernel's EPI_ARGMAX; the 32
-  // lanes of a lane half hold one row's 32 columns
-  auto write_top1 = [&](f32x16 (&v)[RG][CG]) {
-    const int NB = (N + 31) / 32;
-    bool nonfinite = false;
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-      for (int b = 0; b < CG; ++b) {
-        const int n = n0 + col_w + b * 32 + l32;
-#pragma unroll
-        for (int i = 0; i < 16; ++i) {
-          const int mrow = m0 + row_w + a * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
-          uint64_t kv = (mrow < M && n < N) ? pack_logit(v[a][b][i], n, nonfinite) : 0;
-#pragma unroll
-          for (int off = 16; off > 0; off >>= 1) {
-            const uint32_t lo = __shfl_xor((uint32_t)kv, off);
-            const uint32_t hi = __shfl_xor((uint32_t)(kv >> 32), off);
-            const uint64_t o = ((uint64_t)hi << 32) | lo;
-            kv = o > kv ? o : kv;
-          }
-          if (l32 == 0 && mrow < M) part[(size_t)mrow * NB + (n0 + col_w + b * 32) / 32] = kv;
-        }
-      }
-    if (__any(nonfinite) && lane == 0) set_err(err, DVS_ERR_NONFINITE);
-  };
-  if constexpr (!SPLITS) {
-    // 0 + p_0, as in the split paths (keeps the sign of a zero sum alike)
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-      for (int b = 0; b < CG; ++b) acc[a][b] = f32x16{} + acc[a][b];
-    if (part) write_top1(acc);
-    else write_out(acc);
-  } else {
-    if (part) write_top1(sum);
-    else write_out(sum);
-  }
-}
+}  // namespace dvs
+#include "gemm_tile.h"
+namespace dvs {
 
 // fp32: v_mfma_f32_32x32x2_f32; lane (row|col, hh) takes k = k0 + 4*hh + j in
 // MFMA j, so one 16-byte load per operand feeds 4 MFMAs.
@@ -1533,19 +1321,14 @@ struct StepLayout {
       attn_ws, rope, total, attn_bytes, attn_counters;
 };
 
-// Rows per tile when all splits run in one workgroup (more than 32 rows):
-// the largest tile that still gives 256 workgroups, else 32.
-static int gemm_rows_per_tile(int M, int N) {
-  const long long nb = (N + RT_NT - 1) / RT_NT;
-  for (int mt = 256; mt >= 64; mt >>= 1)
-    if (mt / 2 < M && nb * ((M + mt - 1) / mt) >= 256) return mt;
-  return 32;
-}
-
 __global__ void zero_words_kernel(int32_t* __restrict__ p, int n) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0;
 }
+
+// bf16 products over whole 64-k chunks: the GEMMs with fused epilogues
+// (gemm_ws_kernel and its kin, gemm_tile_kernel).
+static bool tiled_gemm(int dtype, int K) { return dtype == DVS_BF16 && K % 64 == 0; }
 
 static size_t al(size_t v) { return (v + 255) & ~(size_t)255; }
 
@@ -1572,8 +1355,11 @@ static StepLayout step_layout(const dvs_model* m, int S, int n_causal, int n_mas
   L.k = off; off += al(M * kd * es);
   L.v = off; off += al(M * kd * es);
   L.att = off; off += al(M * qd * es);
-  L.gate = off; off += al(M * (size_t)m->ffn * es);
-  L.up = off; off += al(M * (size_t)m->ffn * es);
+  // gate and up of the layers whose projections do not take silu(gate) * up
+  // in their epilogue
+  const size_t sep = tiled_gemm(m->dtype, m->hidden) ? 0 : M * (size_t)m->ffn * es;
+  L.gate = off; off += al(sep);
+  L.up = off; off += al(sep);
   L.act = off; off += al(M * (size_t)m->ffn * es);
   L.logits = off; off += al(logit_rows * (size_t)m->vocab * 4);
   L.am = off; off += al(logit_rows * 4);
@@ -1590,8 +1376,8 @@ static StepLayout step_layout(const dvs_model* m, int S, int n_causal, int n_mas
                                        m->head_dim, max_pages, chunk_keys, m->dtype);
   L.attn_ws = off; off += al(L.attn_bytes);
   // the step's rotary (cos, sin) table, for calls whose Q|K|V projection
-  // takes the rotation in its epilogue (up to WS_MAX_ROWS rows)
-  L.rope = off; off += al(M <= (size_t)WS_MAX_ROWS ? M * (m->head_dim / 2) * 16 : 0);
+  // takes the rotation in its epilogue
+  L.rope = off; off += al(tiled_gemm(m->dtype, m->hidden) ? M * (m->head_dim / 2) * 16 : 0);
   L.total = off;
   return L;
 }
@@ -1705,44 +1491,64 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
   return launch_status("draft_verify_step(gemm)");
 }
 
-// gemm_ws_kernel serves a call when it computes the same splits as
-// gemm_rt_kernel would (bf16, K a multiple of 256) and the rows are few.
-static bool use_ws(int dtype, int M, int K) {
-  return dtype == DVS_BF16 && K % (64 * GK_SPLITS) == 0 && M <= WS_MAX_ROWS;
+template <int WM, int WN, int RG, int CG, int NS>
+static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
+  constexpr int MT = WM * RG * 32, CT = WN * CG * 32;
+  g.n_rt = (g.M + MT - 1) / MT;
+  const long long total = (long long)g.n_rt * ((g.ncols + CT - 1) / CT);
+  DVS_CHECK_SUPPORTED(total < (1LL << 30), "draft_verify_step: GEMM grid too large");
+  const dim3 gr((unsigned)((total + 7) / 8 * 8)), blk(WM * WN * 64);
+  switch (g.epi) {
+    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, g); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, g); break;
+    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, g); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, g); break;
+    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, g); break;
+  }
+  return launch_status("draft_verify_step(gemm)");
+}
+
+// The tile of gemm_tile_kernel: the one whose rounds over the chip take
+// least.  A round of tiles at K = 1536 takes about 31 us for 128 x 256 and
+// 21 us for 128 x 128 (one workgroup per CU), 13 us for 64 x 64 (two per CU).
+// Measured against each other in that order (us): 1024 x 1536 outputs
+// 24.2 / 19.3 / 13.4, 1024 x 2304 22.4 / 15.5 / 18.8, 2176 x 1536 26.9 / 22.3
+// / 26.6, 1024 x 8192 30.6 / 36.7 / 47.4, 8832 x 8192 286 / 341 / 452.
+static int launch_tile(GemmArgs& g, hipStream_t st) {
+  const long long cus = device_cus();
+  auto cost = [&](int mt, int ct, int per_cu, int us) {
+    const long long tiles = (long long)((g.M + mt - 1) / mt) * ((g.ncols + ct - 1) / ct);
+    return (tiles + cus * per_cu - 1) / (cus * per_cu) * us;
+  };
+  const long long wide = cost(128, 256, 1, 31), mid = cost(128, 128, 1, 21), small = cost(64, 64, 2, 13);
+  if (wide <= mid && wide <= small) return launch_tile_cfg<2, 4, 2, 2, 3>(g, st);
+  if (mid <= small) return launch_tile_cfg<4, 2, 1, 2, 4>(g, st);
+  return launch_tile_cfg<2, 2, 1, 1, 4>(g, st);
+}
+
+// The weight-streaming kernels serve the calls of few rows whose K has the
+// four logical splits, gemm_tile_kernel the others.
+static bool use_ws(int M, int K) { return K % (64 * GK_SPLITS) == 0 && M <= WS_MAX_ROWS; }
+
+static int launch_gemm(GemmArgs& g, hipStream_t st) {
+  g.ksplit = gemm_ksplit(g.K);
+  return use_ws(g.M, g.K) ? launch_ws(g, st) : launch_tile(g, st);
 }
 
 // C = A W^T (or C += for the fp32 residual).  `c_f32` selects an fp32 output
 // for bf16 models (residual stream, logits); fp32 models always write fp32.
-static int gemm(const StepLayout& L, char* ws, int dtype, const void* A, const void* W, int M,
-                int N, int K, void* C, int c_f32, int accumulate, hipStream_t st) {
-  (void)L; (void)ws;
-  const int waves = (N + 31) / 32;
-  const int blocks = (waves + 3) / 4;
-  if (use_ws(dtype, M, K)) {
+static int gemm(int dtype, const void* A, const void* W, int M, int N, int K, void* C, int c_f32,
+                int accumulate, hipStream_t st) {
+  if (tiled_gemm(dtype, K)) {
     GemmArgs g{};
     g.A = (const __bf16*)A; g.M = M; g.K = K; g.ncols = N;
     g.seg[0] = GemmSeg{(const __bf16*)W, C, 0, N};
     g.nseg = 1;
     g.epi = c_f32 ? (accumulate ? EPI_F32_ADD : EPI_F32) : EPI_BF16;
-    return launch_ws(g, st);
+    return launch_gemm(g, st);
   }
-  if (dtype == DVS_BF16 && K % 64 == 0) {
-    const int ksp = gemm_ksplit(K);
-    int mt = M <= 32 ? 32 : gemm_rows_per_tile(M, N);
-    if (mt == 256 && ksp > 1) mt = 128;   // the 256-row tile keeps no running split sum
-    const int nb = (N + RT_NT - 1) / RT_NT;
-    const long long grid = (long long)nb * ((M + mt - 1) / mt);
-    DVS_CHECK_SUPPORTED(grid < (1LL << 31), "draft_verify_step: GEMM grid too large");
-    const dim3 g((unsigned)grid), blk(256);
-    const __bf16* a = (const __bf16*)A;
-    const __bf16* wt = (const __bf16*)W;
-    switch (mt) {
-      case 256: hipLaunchKernelGGL((gemm_rt_kernel<256, false>), g, blk, 0, st, a, wt, M, N, K, C, c_f32, accumulate, ksp, nullptr, nullptr); break;
-      case 128: hipLaunchKernelGGL((gemm_rt_kernel<128, true>), g, blk, 0, st, a, wt, M, N, K, C, c_f32, accumulate, ksp, nullptr, nullptr); break;
-      case 64: hipLaunchKernelGGL((gemm_rt_kernel<64, true>), g, blk, 0, st, a, wt, M, N, K, C, c_f32, accumulate, ksp, nullptr, nullptr); break;
-      default: hipLaunchKernelGGL((gemm_rt_kernel<32, true>), g, blk, 0, st, a, wt, M, N, K, C, c_f32, accumulate, ksp, nullptr, nullptr); break;
-    }
-  } else if (dtype == DVS_BF16)
+  const int blocks = ((N + 31) / 32 + 3) / 4;
+  if (dtype == DVS_BF16)
     hipLaunchKernelGGL(gemm_bf16_kernel, dim3(blocks), dim3(256), 0, st, (const __bf16*)A,
                        (const __bf16*)W, M, N, K, C, c_f32, accumulate);
   else
@@ -1762,9 +1568,7 @@ static int lm_head_top1(const dvs_model* m, const StepLayout& L, char* ws, const
   g.epi = EPI_ARGMAX;
   g.part = (uint64_t*)(ws + L.part);
   g.err = err;
-  // (calls of more than 32 rows take two 32-column blocks per wave, so each
-  // A chunk serves 64 columns)
-  int rc = launch_ws(g, st);
+  int rc = launch_gemm(g, st);
   if (rc) return rc;
   const int NB = (m->vocab + 31) / 32;
   hipLaunchKernelGGL(argmax_rows_kernel, dim3((unsigned)M), dim3(256), 0, st, g.part,
@@ -1796,7 +1600,8 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
   // the attention's split counters: clear them once; every attention call
   // leaves them zero for the next layer.
   const double log2_theta = log2((double)m->rope_theta);
-  const bool rope_fused = use_ws(dt, M, H) && D % 32 == 0;
+  const bool fused = tiled_gemm(dt, H);         // projections with fused epilogues
+  const bool rope_fused = fused && D % 32 == 0;
   const int nw = (int)(L.attn_counters / 4);
   if (rope_fused) {
     // the rotary table, with the counters' clearing in the same launch
@@ -1814,7 +1619,7 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
     if (l > 0 || !first_norm_done)
       hipLaunchKernelGGL(rmsnorm_kernel<T>, dim3(M), dim3(256), 0, stream, x, (const T*)ly.g_attn, H,
                          m->rms_eps, h);
-    if (use_ws(dt, M, H)) {
+    if (fused) {
       // Q, K and V in one launch (the same splits as three separate calls)
       GemmArgs g{};
       g.A = (const __bf16*)h; g.M = M; g.K = H; g.ncols = (Hq + 2 * Hkv) * D;
@@ -1829,11 +1634,11 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
         g.rope_tab = (const double2*)(ws + L.rope);
         g.rope_D = D;
       }
-      if ((rc = launch_ws(g, stream))) return rc;
+      if ((rc = launch_gemm(g, stream))) return rc;
     } else {
-      if ((rc = gemm(L, ws, dt, h, ly.wq, M, Hq * D, H, q, 0, 0, stream))) return rc;
-      if ((rc = gemm(L, ws, dt, h, ly.wk, M, Hkv * D, H, k, 0, 0, stream))) return rc;
-      if ((rc = gemm(L, ws, dt, h, ly.wv, M, Hkv * D, H, v, 0, 0, stream))) return rc;
+      if ((rc = gemm(dt, h, ly.wq, M, Hq * D, H, q, 0, 0, stream))) return rc;
+      if ((rc = gemm(dt, h, ly.wk, M, Hkv * D, H, k, 0, 0, stream))) return rc;
+      if ((rc = gemm(dt, h, ly.wv, M, Hkv * D, H, v, 0, 0, stream))) return rc;
     }
     if (!rope_fused) {
       const long long nqk = (long long)M * (Hq + Hkv) * (D / 2);
@@ -1847,11 +1652,11 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
                                    chunk_keys, att, st->err_word, ws + L.attn_ws, L.attn_bytes,
                                    stream);
     if (rc) return rc;
-    if ((rc = gemm(L, ws, dt, att, ly.wo, M, H, Hq * D, x, 1, 1, stream))) return rc;
+    if ((rc = gemm(dt, att, ly.wo, M, H, Hq * D, x, 1, 1, stream))) return rc;
     if (m->ffn > 0) {
       hipLaunchKernelGGL(rmsnorm_kernel<T>, dim3(M), dim3(256), 0, stream, x, (const T*)ly.g_mlp,
                          H, m->rms_eps, h);
-      if (use_ws(dt, M, H)) {
+      if (fused) {
         // gate and up in one launch, silu(gate) * up in its epilogue
         GemmArgs g{};
         g.A = (const __bf16*)h; g.M = M; g.K = H; g.ncols = 32 * ((m->ffn + 15) / 16);
@@ -1859,16 +1664,16 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
         g.seg[1] = GemmSeg{(const __bf16*)ly.w_up, nullptr, 0, m->ffn};
         g.nseg = 2;
         g.epi = EPI_SWIGLU;
-        if ((rc = launch_ws(g, stream))) return rc;
+        if ((rc = launch_gemm(g, stream))) return rc;
       } else {
-        if ((rc = gemm(L, ws, dt, h, ly.w_gate, M, m->ffn, H, gate, 0, 0, stream))) return rc;
-        if ((rc = gemm(L, ws, dt, h, ly.w_up, M, m->ffn, H, up, 0, 0, stream))) return rc;
+        if ((rc = gemm(dt, h, ly.w_gate, M, m->ffn, H, gate, 0, 0, stream))) return rc;
+        if ((rc = gemm(dt, h, ly.w_up, M, m->ffn, H, up, 0, 0, stream))) return rc;
         const long long n = (long long)M * m->ffn;
         hipLaunchKernelGGL(silu_mul_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                            stream, gate, up, n, act);
         if ((rc = launch_status("draft_verify_step(silu)"))) return rc;
       }
-      if ((rc = gemm(L, ws, dt, act, ly.w_down, M, H, m->ffn, x, 1, 1, stream))) return rc;
+      if ((rc = gemm(dt, act, ly.w_down, M, H, m->ffn, x, 1, 1, stream))) return rc;
     }
   }
   hipLaunchKernelGGL(rmsnorm_kernel<T>, dim3(M), dim3(256), 0, stream, x, (const T*)m->g_final, H,
@@ -1897,11 +1702,11 @@ static int run_step(const dvs_model* m, const dvs_state* st, int n_causal, int n
   if ((rc = launch_status("draft_verify_step(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, n_causal, n_mask, chunk_keys, L, ws, stream, group, embed_norm)))
     return rc;
-  if (!logits_out && use_ws(m->dtype, M, m->hidden)) {
+  if (!logits_out && tiled_gemm(m->dtype, m->hidden)) {
     // top-1 in the LM head's epilogue: the logits never reach memory
     if ((rc = lm_head_top1(m, L, ws, ws + L.h, M, am, st->err_word, stream))) return rc;
   } else {
-    if ((rc = gemm(L, ws, m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0,
+    if ((rc = gemm(m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0,
                    stream)))
       return rc;
     rc = argmax_accept(logits, DVS_F32, S, R, m->vocab, n_causal, st->draft, st->draft_width, am,
@@ -1935,7 +1740,7 @@ static int run_round(const dvs_model* m, const dvs_state* st, int B, int chunk_k
                      nullptr, 0, (float*)(ws + L.x));
   if ((rc = launch_status("literal_round(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, 1, B, chunk_keys, L, ws, stream))) return rc;
-  if ((rc = gemm(L, ws, m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
     return rc;
   rc = argmax_accept(logits, DVS_F32, S, R, m->vocab, 1, st->draft, st->draft_width, am, acc,
                      st->err_word, stream);
@@ -1949,7 +1754,7 @@ static int run_round(const dvs_model* m, const dvs_state* st, int B, int chunk_k
                      (float*)(ws + L.x));
   if ((rc = launch_status("literal_round(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, R, 0, chunk_keys, L, ws, stream))) return rc;
-  if ((rc = gemm(L, ws, m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
     return rc;
   rc = argmax_accept(logits, DVS_F32, S, R, m->vocab, R, st->draft, st->draft_width, am, acc,
                      st->err_word, stream);
@@ -1981,7 +1786,7 @@ static int run_denoise(const dvs_model* m, const dvs_state* st, int B, int npos,
   int rc;
   if ((rc = launch_status("diffusion_denoise(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, 1, B, chunk_keys, L, ws, stream))) return rc;
-  if ((rc = gemm(L, ws, m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, ws + L.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0, stream)))
     return rc;
   if ((rc = top1_confidence(logits, DVS_F32, M, m->vocab, am, conf, st->err_word, stream))) return rc;
   hipLaunchKernelGGL(zero_words_kernel, dim3(1), dim3(256), 0, stream, n_open, 1);
@@ -2054,7 +1859,7 @@ static int run_round_refined(const dvs_model* m, const dvs_state* st, int B, flo
                      (float*)(ws + Lv.x));
   if ((rc = launch_status("literal_round_refined(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, R, 0, chunk_keys, Lv, ws, stream))) return rc;
-  if ((rc = gemm(Lv, ws, m->dtype, ws + Lv.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0,
+  if ((rc = gemm(m->dtype, ws + Lv.h, m->lm_head, M, m->vocab, m->hidden, logits, 1, 0,
                  stream)))
     return rc;
   rc = argmax_accept(logits, DVS_F32, S, R, m->vocab, R, st->draft, st->draft_width, am, acc,
@@ -2091,7 +1896,7 @@ static int run_round_sampled(const dvs_model* m, const dvs_state* st, int B, flo
                      (float*)(ws + Ld.x));
   if ((rc = launch_status("literal_round_sampled(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, 1, B, chunk_keys, Ld, ws, stream))) return rc;
-  if ((rc = gemm(Ld, ws, m->dtype, ws + Ld.h, m->lm_head, M, V, m->hidden, zd, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, ws + Ld.h, m->lm_head, M, V, m->hidden, zd, 1, 0, stream)))
     return rc;
   if ((rc = launch_row_stats(zd, M, V, invT, sd, st->err_word, stream))) return rc;
   if ((rc = launch_sample_rows(zd, sd, V, invT, u, us, S, R, tok, stream))) return rc;
@@ -2103,7 +1908,7 @@ static int run_round_sampled(const dvs_model* m, const dvs_state* st, int B, flo
                      (float*)(ws + Lv.x));
   if ((rc = launch_status("literal_round_sampled(embed)"))) return rc;
   if ((rc = forward_layers<T>(m, st, R, 0, chunk_keys, Lv, ws, stream))) return rc;
-  if ((rc = gemm(Lv, ws, m->dtype, ws + Lv.h, m->lm_head, M, V, m->hidden, zv, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, ws + Lv.h, m->lm_head, M, V, m->hidden, zv, 1, 0, stream)))
     return rc;
   if ((rc = launch_row_stats(zv, M, V, invT, sv, st->err_word, stream))) return rc;
   if ((rc = launch_accept_final(S, B, V, invT, zv, sv, zd, sd, st->draft, st->draft_width, u, us,
@@ -2130,7 +1935,7 @@ static int run_prefill(const dvs_model* m, const dvs_state* st, int P, int n_mas
   hipLaunchKernelGGL(gather_rows_kernel<T>, dim3(S * nsel), dim3(256), 0, stream,
                      (const T*)(ws + L.h), m->hidden, R, P - 1, nsel, hsel);
   float* logits = logits_out ? logits_out : (float*)(ws + L.logits);
-  if ((rc = gemm(L, ws, m->dtype, hsel, m->lm_head, S * nsel, m->vocab, m->hidden, logits, 1, 0, stream)))
+  if ((rc = gemm(m->dtype, hsel, m->lm_head, S * nsel, m->vocab, m->hidden, logits, 1, 0, stream)))
     return rc;
   int32_t* am = (int32_t*)(ws + L.am);
   int32_t* acc = (int32_t*)(ws + L.acc);

@@ -1,0 +1,88 @@
+"""GPU: the many-row decoder GEMM (gemm_tile_kernel) through
+draft_verify_step -- every tile size and epilogue, rows and columns that end
+inside a tile, K with one and with four logical splits -- against the float64
+oracle, its fused top-1 against the logits, and its rows bit for bit against
+the few-row kernels'."""
+import dataclasses
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import decode as od
+from oracle.model import OracleModel
+from paper_2609_26638_amd import dvs, synth
+from tests.gpu_util import max_rel_err, to_dev
+
+pytestmark = pytest.mark.gpu
+
+
+def _model(H, Hq, Hkv, D, ffn, V, S, nc, nm):
+    w = synth.make_model_weights(11, V, H, Hq, Hkv, D, 1, ffn, std=0.08)
+    lens = [(37 + 61 * s) % 200 for s in range(S)]
+    ai = synth.make_attn_inputs(11, S, lens, nc, nm, Hq, Hkv, D, "bf16", std=0.5, scatter=True,
+                                extra_pages=4 * S)
+    rng = np.random.default_rng(5)
+    ai.state.boundary[:] = rng.integers(0, V, size=S)
+    ai.state.draft[:] = rng.integers(0, V, size=ai.state.draft.shape)
+    return w, ai
+
+
+def _step(w, ai, host, nc, nm):
+    """(logits [S, R, V], top-1 with the logits, top-1 without)"""
+    S, R = host.kv_len.shape[0], nc + nm
+    lg = torch.empty((S, R, w.V), dtype=torch.float32, device="cuda")
+    ams = []
+    for logits in (lg, None):
+        dm = dvs.DeviceModel(w, [to_dev(ai.k_pool, "bf16")], [to_dev(ai.v_pool, "bf16")], "bf16")
+        st = dvs.DeviceState(host)
+        am = torch.empty((S, R), dtype=torch.int32, device="cuda")
+        dvs.draft_verify_step(dm, st, nc, nm, logits_out=logits, argmax_out=am)
+        assert int(st.err.item()) == 0
+        ams.append(am.cpu().numpy())
+    return lg.cpu().numpy(), ams[0], ams[1]
+
+
+# (hidden, heads, kv heads, head dim, ffn, vocab, sequences, causal, mask):
+# 520 rows: 64 x 64 tiles for the layer, 128 x 256 for the head (odd vocab);
+# the same rows with a head of 128 x 128 tiles; 257 rows with one K split and
+# a last column block of 8; 3 rows with one K split and K of three chunks.
+@pytest.mark.parametrize("H,Hq,Hkv,D,ffn,V,S,nc,nm", [
+    (256, 4, 2, 64, 512, 33001, 13, 20, 20),
+    (256, 2, 1, 128, 512, 5000, 13, 40, 0),
+    (320, 5, 1, 64, 448, 1000, 1, 257, 0),
+    (192, 2, 2, 96, 192, 515, 1, 2, 1),
+])
+def test_many_row_step_matches_oracle(H, Hq, Hkv, D, ffn, V, S, nc, nm):
+    w, ai = _model(H, Hq, Hkv, D, ffn, V, S, nc, nm)
+    rnd = lambda a: synth.bf16_to_f32(synth.f32_to_bf16_bits(a))
+    wb = dataclasses.replace(w, **{
+        f.name: [rnd(a) for a in v] if isinstance(v, list) else rnd(v)
+        for f in dataclasses.fields(w)
+        if isinstance(v := getattr(w, f.name), (list, np.ndarray))})
+    om = OracleModel(wb, [synth.bf16_to_f32(ai.k_pool)], [synth.bf16_to_f32(ai.v_pool)])
+    tok = np.full((S, nc + nm), V, np.int64)
+    tok[:, 0] = ai.state.boundary
+    tok[:, 1:nc] = ai.state.draft[:, :nc - 1]
+    ref = om.forward(om.embed[tok], ai.state.copy(), nc, nm)
+    lg, am, am2 = _step(w, ai, ai.state, nc, nm)
+    # bf16 activations between the layer's kernels: a few 1e-3 of the largest
+    # logit each, as for the few-row steps
+    assert max_rel_err(lg.astype(np.float64), ref) <= 5e-2
+    np.testing.assert_array_equal(am, od.top1_rows(lg.astype(np.float64)))
+    np.testing.assert_array_equal(am2, am)
+
+
+def test_rows_equal_the_few_row_kernels():
+    """520 rows in one call, then each of two sequences alone (40 rows)."""
+    S, nc, nm = 13, 20, 20
+    w, ai = _model(256, 4, 2, 64, 512, 33001, S, nc, nm)
+    lg, am, _ = _step(w, ai, ai.state, nc, nm)
+    for s in (0, S - 1):
+        h = ai.state.copy()
+        for f in ("kv_len", "page_table", "num_pages", "boundary", "draft", "out_tokens",
+                  "out_count", "finished"):
+            setattr(h, f, getattr(h, f)[s:s + 1].copy())
+        one, am1, _ = _step(w, ai, h, nc, nm)
+        np.testing.assert_array_equal(one[0], lg[s])
+        np.testing.assert_array_equal(am1[0], am[s])
