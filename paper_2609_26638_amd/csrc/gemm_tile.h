@@ -26,17 +26,6 @@
 
 namespace dvs {
 
-// A workgroup barrier for rings of direct global -> LDS copies: it completes
-// this wave's LDS reads and leaves direct global -> LDS copies in flight
-// (__syncthreads() waits for every outstanding load first, which would drain
-// the ring at each chunk).  The caller has waited for the copies it needs.
-__device__ __forceinline__ void ring_barrier() {
-  asm volatile("" ::: "memory");
-  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
-  __builtin_amdgcn_s_barrier();
-  asm volatile("" ::: "memory");
-}
-
 // The epilogue of a tile of MT x CT summed values in LDS (fp32, row-major),
 // by NT threads.  Columns past the call's are skipped; a 32-column block lies
 // in one segment.

@@ -533,6 +533,17 @@ __device__ __forceinline__ void ws_wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xF) | ((N >> 4) << 14) | (0x7 << 4) | (0xF << 8));
 }
 
+// A workgroup barrier for rings of direct global -> LDS copies: it completes
+// this wave's LDS reads and leaves direct global -> LDS copies in flight
+// (__syncthreads() waits for every outstanding load first, which would drain
+// the ring at each chunk).  The caller has waited for the copies it needs.
+__device__ __forceinline__ void ring_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 // The epilogue of a weight-streaming GEMM tile (MT rows x CB 32-column
 // blocks of CW kept columns): s_red holds NSP planes [NSP][MT][CB * 32] of
 // fp32 partial sums (the splits, or one plane already summed in order),
@@ -1009,7 +1020,7 @@ gemm_ns_kernel(GemmArgs g) {
       // this wave's copies of chunk t are in; the barrier makes everyone's
       // (the A rows are shared) and frees the slot chunk t-1 used
       wait_chunk(min(NS - 2, nch - 1 - t));
-      __syncthreads();
+      ring_barrier();
       if (t + NS - 1 < nch) issue(t + NS - 1);
       const char* stage = s_ring + (t % NS) * STB;
       bf16x8 bw[KC / 16], ba[KC / 16][RG];
@@ -1058,31 +1069,25 @@ gemm_ns_kernel(GemmArgs g) {
   ws_epilogue<MT, NS_BLOCKS, CW, EPI, 1>(g, s_sum, tid, lane, m0, cg, si, NB, false);
 }
 
-// gemm_nk_kernel<EPI, SPLIT_M>: 64-row tiles with the four waves split 2 x
-// 2, each over one K half, that is splits 2h and 2h+1, whose sums it keeps
-// apart (each the in-order MFMA accumulation over its K range, exactly
-// gemm_ws_kernel's p_s):
-//   SPLIT_M = false: two 32-column blocks; wave w takes block w & 1 over K
-//     half w >> 1, and the two waves of a half share its A chunk;
-//   SPLIT_M = true: one 32-column block; wave w takes rows 32 (w & 1) ..
-//     over K half w >> 1, and the two waves of a half share its weight
-//     chunk (and the Q|K|V projection's rotary epilogue is available).
-// Chunks are 64 k wide (whole 128-byte lines) in rings that leave room for
-// two workgroups per CU (2 stages of 32 KB, or 3 of 24 KB).  The four split
-// sums meet in LDS and the shared epilogue adds them in order:
-// bit-identical to gemm_ws_kernel.
-template <int EPI, bool SPLIT_M>
+// gemm_nk_kernel: 64 rows x one 32-column block, the four waves split 2 x 2:
+// wave w takes rows 32 (w & 1) .. over K half w >> 1, that is splits 2h and
+// 2h+1, whose sums it keeps apart (each the in-order MFMA accumulation over
+// its K range, exactly gemm_ws_kernel's p_s); the two waves of a half share
+// its weight chunk.  64-k chunks (whole 128-byte lines) in rings of three
+// 24 KB stages leave room for two workgroups per CU.  The four split sums
+// meet in LDS and the shared epilogue adds them in order: bit-identical to
+// gemm_ws_kernel.  Serves Q|K|V (rotary epilogue) of calls of more than one
+// workgroup per CU.
 __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   constexpr int MT = 64, CW = 32, KC = 64, RB = KC * 2;
-  constexpr int CB = SPLIT_M ? 1 : 2;           // blocks per tile
-  constexpr int RG = SPLIT_M ? 1 : 2;           // 32-row groups per wave
+  constexpr int CB = 1, EPI = EPI_BF16;
   constexpr int AB = MT * RB;                   // one K half's A chunk: 8 KB
   constexpr int WB = 32 * RB;                   // one block's weight rows: 4 KB
-  constexpr int STB = 2 * AB + 2 * CB * WB;     // A of both halves, W of (block, half)
-  constexpr int NS = SPLIT_M ? 3 : 2;
+  constexpr int STB = 2 * AB + 2 * WB;          // A and W of both halves
+  constexpr int NS = 3;
   constexpr int TW = CB * 32;
   constexpr int AI = 4;                         // A copies per wave and chunk (32 rows)
-  constexpr int WIW = SPLIT_M ? 2 : 4;          // W copies per wave and chunk
+  constexpr int WIW = 2;                        // W copies per wave and chunk
   constexpr int NPL = AI + WIW;
   static_assert(NS * STB >= GK_SPLITS * MT * TW * 4, "the split sums reuse the ring");
   static_assert(NS * STB <= 81920, "two workgroups per CU");
@@ -1090,7 +1095,7 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int wl = w & 1, kh = w >> 1;            // block (or row group) and K half of this wave
+  const int wl = w & 1, kh = w >> 1;            // row group and K half of this wave
   const int NB = (g.ncols + CW - 1) / CW;
   const int NG = (NB + CB - 1) / CB;
   const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
@@ -1100,35 +1105,27 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   const int crow = lane >> 3, cchk = lane & 7;
   auto sw = [](int row) { return (row >> 1) & 7; };
   int si = 0;
-  if (EPI != EPI_SWIGLU)
-    while (si + 1 < g.nseg && cg * CB * CW >= g.seg[si + 1].n0) ++si;
+  while (si + 1 < g.nseg && cg * CB * CW >= g.seg[si + 1].n0) ++si;
   const bool rope = EPI == EPI_BF16 && g.rope_tab != nullptr && si < 2;
-  const int cb = cg * CB + (SPLIT_M ? 0 : wl);  // this wave's block
-  // weight rows this wave copies: all 32 of its block (SPLIT_M = false), or
-  // rows 16 (w & 1) .. + 15 of the shared block (SPLIT_M = true)
+  const int cb = cg;
+  // weight rows this wave copies: rows 16 (w & 1) .. + 15 of the shared block
   const __bf16* wsrc[WIW];
 #pragma unroll
   for (int i = 0; i < WIW; ++i) {
-    const int r = (SPLIT_M ? 16 * wl : 0) + 8 * i + crow;
+    const int r = 16 * wl + 8 * i + crow;
     const __bf16* base;
     bool valid;
     int rowi;
-    if (EPI == EPI_SWIGLU) {
-      rowi = cb * 16 + (r & 15);
-      valid = rowi < g.seg[0].n;
-      base = r < 16 ? g.seg[0].W : g.seg[1].W;
-    } else {
-      rowi = cb * CW - g.seg[si].n0 + r;
-      if (rope) {
-        // block bh of a head holds dims bh*16 .. bh*16+15 and their
-        // rotate-half partners D/2 + bh*16 ..
-        const int hd = rowi / g.rope_D, cp = rowi - hd * g.rope_D;
-        const int bh = cp / CW, c = cp - bh * CW;
-        rowi = hd * g.rope_D + (c < CW / 2 ? bh * (CW / 2) + c : g.rope_D / 2 + bh * (CW / 2) + c - CW / 2);
-      }
-      valid = rowi < g.seg[si].n;
-      base = g.seg[si].W;
+    rowi = cb * CW - g.seg[si].n0 + r;
+    if (rope) {
+      // block bh of a head holds dims bh*16 .. bh*16+15 and their
+      // rotate-half partners D/2 + bh*16 ..
+      const int hd = rowi / g.rope_D, cp = rowi - hd * g.rope_D;
+      const int bh = cp / CW, c = cp - bh * CW;
+      rowi = hd * g.rope_D + (c < CW / 2 ? bh * (CW / 2) + c : g.rope_D / 2 + bh * (CW / 2) + c - CW / 2);
     }
+    valid = rowi < g.seg[si].n;
+    base = g.seg[si].W;
     wsrc[i] = base + (size_t)(valid ? rowi : 0) * g.K + ((cchk ^ sw(r)) << 3);
   }
   const __bf16* asrc[AI];                       // A rows 32 (w & 1) + 8i + L/8 of half kh
@@ -1140,8 +1137,7 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   const int kh0 = kh * (g.K / 2);               // first k of this wave's half
   const int nch = g.K / 2 / KC;                 // chunks per half (even: K % 256 == 0)
   const int cps = nch / 2;                      // chunks per split
-  // stage layout: A of half 0, A of half 1, then W of (block or half) slots
-  auto wslot = [&](int blk, int half) { return 2 * AB + (SPLIT_M ? half : 2 * half + blk) * WB; };
+  const int wsl0 = 2 * AB + kh * WB;            // stage layout: A of half 0, A of half 1, W of half 0, W of half 1
   auto issue = [&](int t) {
     char* stage = s_ring + (t % NS) * STB;
     const int k0 = kh0 + t * KC;
@@ -1152,7 +1148,7 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
 #pragma unroll
     for (int i = 0; i < WIW; ++i)
       __builtin_amdgcn_global_load_lds((const void*)(wsrc[i] + k0),
-                                       (__attribute__((address_space(3))) void*)(stage + wslot(wl, kh) + ((SPLIT_M ? 2 * wl : 0) + i) * 1024), 16, 0, 0);
+                                       (__attribute__((address_space(3))) void*)(stage + wsl0 + (2 * wl + i) * 1024), 16, 0, 0);
   };
   auto wait_chunk = [&](int later) {
     static_for<0, NS>([&](auto c) {
@@ -1160,11 +1156,8 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
       if (later == n) ws_wait_vmcnt<n * NPL>();
     });
   };
-  f32x16 acc[2][RG];
-#pragma unroll
-  for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int a = 0; a < RG; ++a) acc[sp][a] = f32x16{};
+  f32x16 acc[2];
+  acc[0] = acc[1] = f32x16{};
   static_for<0, NS - 1>([&](auto c) {
     if (decltype(c)::value < nch) issue(decltype(c)::value);
   });
@@ -1175,53 +1168,41 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
       // this wave's copies of chunk t are in; the barrier makes the
       // partner's, and frees the slot chunk t-1 used
       wait_chunk(min(NS - 2, nch - 1 - t));
-      __syncthreads();
+      ring_barrier();
       if (t + NS - 1 < nch) issue(t + NS - 1);
       const char* stage = s_ring + (t % NS) * STB;
-      const char* wsl = stage + wslot(wl, kh);
-      bf16x8 bwf[KC / 16], ba[KC / 16][RG];
+      const char* wsl = stage + wsl0;
+      bf16x8 bwf[KC / 16], ba[KC / 16];
 #pragma unroll
       for (int ks = 0; ks < KC / 16; ++ks) {
         const int q = 2 * ks + hh;
         bwf[ks] = *(const bf16x8*)(wsl + l32 * RB + ((q ^ sw(l32)) << 4));
-#pragma unroll
-        for (int a = 0; a < RG; ++a) {
-          const int r = (SPLIT_M ? 32 * wl : a * 32) + l32;
-          ba[ks][a] = *(const bf16x8*)(stage + kh * AB + r * RB + ((q ^ sw(r)) << 4));
-        }
+        const int r = 32 * wl + l32;
+        ba[ks] = *(const bf16x8*)(stage + kh * AB + r * RB + ((q ^ sw(r)) << 4));
       }
 #pragma unroll
       for (int ks = 0; ks < KC / 16; ++ks) {
         asm volatile("" : "+v"(bwf[ks]));
-#pragma unroll
-        for (int a = 0; a < RG; ++a) asm volatile("" : "+v"(ba[ks][a]));
+        asm volatile("" : "+v"(ba[ks]));
       }
 #pragma unroll
       for (int ks = 0; ks < KC / 16; ++ks)
-#pragma unroll
-        for (int a = 0; a < RG; ++a)
-          acc[sp][a] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ba[ks][a], bwf[ks], acc[sp][a], 0, 0, 0);
+        acc[sp] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(ba[ks], bwf[ks], acc[sp], 0, 0, 0);
     }
   });
 
   // the four split sums to LDS as planes [split][row][TW] (the ring is free
   // once every wave is done); rows of W past the segment end were read from
   // row 0: their columns are 0
-  bool wvalid;
-  if (EPI == EPI_SWIGLU) wvalid = cb * 16 + (l32 & 15) < g.seg[0].n;
-  else wvalid = cb * CW - g.seg[si].n0 + l32 < g.seg[si].n;
+  const bool wvalid = cb * CW - g.seg[si].n0 + l32 < g.seg[si].n;
   __syncthreads();
   float* s_red = (float*)s_ring;
 #pragma unroll
   for (int sp = 0; sp < 2; ++sp)
-#pragma unroll
-    for (int a = 0; a < RG; ++a)
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int row = (SPLIT_M ? 32 * wl : a * 32) + 8 * (i >> 2) + 4 * hh + (i & 3);
-        s_red[(2 * kh + sp) * (MT * TW) + row * TW + (SPLIT_M ? 0 : wl * 32) + l32] =
-            wvalid ? acc[sp][a][i] : 0.f;
-      }
+    for (int i = 0; i < 16; ++i) {
+      const int row = 32 * wl + 8 * (i >> 2) + 4 * hh + (i & 3);
+      s_red[(2 * kh + sp) * (MT * TW) + row * TW + l32] = wvalid ? acc[sp][i] : 0.f;
+    }
   __syncthreads();
   ws_epilogue<MT, CB, CW, EPI, GK_SPLITS>(g, s_red, tid, lane, m0, cg, si, NB, rope);
 }
@@ -1382,6 +1363,41 @@ static StepLayout step_layout(const dvs_model* m, int S, int n_causal, int n_mas
   return L;
 }
 
+template <int WM, int WN, int RG, int CG, int NS>
+static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
+  constexpr int MT = WM * RG * 32, CT = WN * CG * 32;
+  g.n_rt = (g.M + MT - 1) / MT;
+  const long long total = (long long)g.n_rt * ((g.ncols + CT - 1) / CT);
+  DVS_CHECK_SUPPORTED(total < (1LL << 30), "draft_verify_step: GEMM grid too large");
+  const dim3 gr((unsigned)((total + 7) / 8 * 8)), blk(WM * WN * 64);
+  switch (g.epi) {
+    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, g); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, g); break;
+    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, g); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, g); break;
+    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, g); break;
+  }
+  return launch_status("draft_verify_step(gemm)");
+}
+
+// The tile of gemm_tile_kernel: the one whose rounds over the chip take
+// least.  A round of tiles at K = 1536 takes about 31 us for 128 x 256 and
+// 21 us for 128 x 128 (one workgroup per CU), 13 us for 64 x 64 (two per CU).
+// Measured against each other in that order (us): 1024 x 1536 outputs
+// 24.2 / 19.3 / 13.4, 1024 x 2304 22.4 / 15.5 / 18.8, 2176 x 1536 26.9 / 22.3
+// / 26.6, 1024 x 8192 30.6 / 36.7 / 47.4, 8832 x 8192 286 / 341 / 452.
+static int launch_tile(GemmArgs& g, hipStream_t st) {
+  const long long cus = device_cus();
+  auto cost = [&](int mt, int ct, int per_cu, int us) {
+    const long long tiles = (long long)((g.M + mt - 1) / mt) * ((g.ncols + ct - 1) / ct);
+    return (tiles + cus * per_cu - 1) / (cus * per_cu) * us;
+  };
+  const long long wide = cost(128, 256, 1, 31), mid = cost(128, 128, 1, 21), small = cost(64, 64, 2, 13);
+  if (wide <= mid && wide <= small) return launch_tile_cfg<2, 4, 2, 2, 3>(g, st);
+  if (mid <= small) return launch_tile_cfg<4, 2, 1, 2, 4>(g, st);
+  return launch_tile_cfg<2, 2, 1, 1, 4>(g, st);
+}
+
 template <int MT, int CWT, int CB, bool WK, bool FEW>
 static void launch_ws_epi(const GemmArgs& g, dim3 gr, hipStream_t st) {
   const dim3 blk(256);
@@ -1449,13 +1465,17 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
     };
     if ((NB / 2) * g.n_rt >= WS_WIDE_MIN_WG && groups_ok(2)) CB = 2;
   }
-  // 64-row calls with many 128-column groups and a top-1 or fp32 epilogue
-  // (the LM head): the column-split kernel (one A chunk per four blocks)
+  // calls with many 128-column groups and a top-1 or fp32 epilogue (the LM
+  // head): up to 64 rows the column-split kernel (one A chunk per four
+  // blocks; one row tile, weights read once), above that the many-row tiles
+  // (65,536 columns, K = 1536: 136 rows 63 against 74 us, 256 rows 69
+  // against 101 us; at 64 rows 36 against 34 us)
   if (MT == 64 && !narrow && (g.epi == EPI_ARGMAX || g.epi == EPI_F32)) {
     const int NGn = (NB + NS_BLOCKS - 1) / NS_BLOCKS;
     bool ok = (long long)NGn * g.n_rt >= WS_WIDE_MIN_WG;
     for (int i = 0; i < g.nseg; ++i)
       if (g.seg[i].n0 % (32 * NS_BLOCKS)) ok = false;
+    if (ok && g.M > 64) return launch_tile(g, st);
     if (ok) {
       const long long gridn = (long long)((NGn + 7) / 8) * 8 * g.n_rt;
       DVS_CHECK_SUPPORTED(gridn < (1LL << 31), "draft_verify_step: GEMM grid too large");
@@ -1471,16 +1491,23 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
   const dim3 gr((unsigned)grid);
   // calls of at most one workgroup per CU: whole-line chunks, deeper rings
   const bool wk = (long long)NG * g.n_rt <= device_cus();
-  // 64-row calls of more than one workgroup per CU: whole-line chunks with
-  // the waves split 2 x 2 (two blocks or two row groups, two K halves), so
-  // that the rings still leave room for two workgroups per CU (gate|up
-  // 20.8 -> 18.6 us per launch at 256 rows)
+  // gate|up of more than one workgroup of two blocks per CU: 128 x 64 tiles
+  // of eight waves, each weight read by at most two workgroups (256 rows x
+  // 8192 columns 11.6 against 13.8 us for 64-row tiles split over K halves,
+  // 136 rows 10.9 against 12.8; 4.5 us per layer of a step whose weights
+  // come from HBM)
   if (MT == 64 && CB == 2 && !wk && g.epi == EPI_SWIGLU) {
-    hipLaunchKernelGGL((gemm_nk_kernel<EPI_SWIGLU, false>), gr, dim3(256), 0, st, g);
+    constexpr int TM = 128, TC = 64;
+    g.n_rt = (g.M + TM - 1) / TM;
+    const long long total = (long long)g.n_rt * ((g.ncols + TC - 1) / TC);
+    hipLaunchKernelGGL((gemm_tile_kernel<4, 2, 1, 1, 4, EPI_SWIGLU>), dim3((unsigned)((total + 7) / 8 * 8)),
+                       dim3(512), 0, st, g);
     return launch_status("draft_verify_step(gemm)");
   }
+  // Q|K|V of more than one workgroup per CU: two row groups times two K
+  // halves per workgroup, whole-line chunks, two workgroups per CU
   if (MT == 64 && CB == 1 && !wk && g.epi == EPI_BF16) {
-    hipLaunchKernelGGL((gemm_nk_kernel<EPI_BF16, true>), gr, dim3(256), 0, st, g);
+    hipLaunchKernelGGL((gemm_nk_kernel), gr, dim3(256), 0, st, g);
     return launch_status("draft_verify_step(gemm)");
   }
   if (cw == 8) launch_ws_k<32, 8, 1>(g, gr, wk, st);
@@ -1489,41 +1516,6 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
   else if (CB == 2) launch_ws_k<64, 32, 2>(g, gr, wk, st);
   else launch_ws_k<64, 32, 1>(g, gr, wk, st);
   return launch_status("draft_verify_step(gemm)");
-}
-
-template <int WM, int WN, int RG, int CG, int NS>
-static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
-  constexpr int MT = WM * RG * 32, CT = WN * CG * 32;
-  g.n_rt = (g.M + MT - 1) / MT;
-  const long long total = (long long)g.n_rt * ((g.ncols + CT - 1) / CT);
-  DVS_CHECK_SUPPORTED(total < (1LL << 30), "draft_verify_step: GEMM grid too large");
-  const dim3 gr((unsigned)((total + 7) / 8 * 8)), blk(WM * WN * 64);
-  switch (g.epi) {
-    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, g); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, g); break;
-    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, g); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, g); break;
-    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, g); break;
-  }
-  return launch_status("draft_verify_step(gemm)");
-}
-
-// The tile of gemm_tile_kernel: the one whose rounds over the chip take
-// least.  A round of tiles at K = 1536 takes about 31 us for 128 x 256 and
-// 21 us for 128 x 128 (one workgroup per CU), 13 us for 64 x 64 (two per CU).
-// Measured against each other in that order (us): 1024 x 1536 outputs
-// 24.2 / 19.3 / 13.4, 1024 x 2304 22.4 / 15.5 / 18.8, 2176 x 1536 26.9 / 22.3
-// / 26.6, 1024 x 8192 30.6 / 36.7 / 47.4, 8832 x 8192 286 / 341 / 452.
-static int launch_tile(GemmArgs& g, hipStream_t st) {
-  const long long cus = device_cus();
-  auto cost = [&](int mt, int ct, int per_cu, int us) {
-    const long long tiles = (long long)((g.M + mt - 1) / mt) * ((g.ncols + ct - 1) / ct);
-    return (tiles + cus * per_cu - 1) / (cus * per_cu) * us;
-  };
-  const long long wide = cost(128, 256, 1, 31), mid = cost(128, 128, 1, 21), small = cost(64, 64, 2, 13);
-  if (wide <= mid && wide <= small) return launch_tile_cfg<2, 4, 2, 2, 3>(g, st);
-  if (mid <= small) return launch_tile_cfg<4, 2, 1, 2, 4>(g, st);
-  return launch_tile_cfg<2, 2, 1, 1, 4>(g, st);
 }
 
 // The weight-streaming kernels serve the calls of few rows whose K has the
