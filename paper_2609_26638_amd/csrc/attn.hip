@@ -22,17 +22,26 @@
 //                             B = P packed to bf16 straight from the scores.
 //   A workgroup first appends the window keys of its own tiles ([L, T) from
 //   k_new / v_new) to their pool slots; then every tile, cache or window, is
-//   copied HBM -> LDS with direct 16-byte loads through a 3-stage ring.  The
+//   copied HBM -> LDS with direct 16-byte loads through a ring.  The
 //   tiles that reach L are masked; in the tile that runs past T the keys >= T
 //   read the sequence's last page again and their V values are zeroed before
 //   the products (their weights are zero, and a non-finite stale value would
 //   otherwise make them NaN).
 //
 //   Two ways to cut the work (both deterministic):
-//   * aligned (chunk_keys > 0): workgroup = one chunk of one item, chunks at
-//     absolute multiples of chunk_keys, so a row's arithmetic never depends
+//   * aligned (chunk_keys > 0): chunks at absolute multiples of chunk_keys,
+//     each with a partial of its own, so a row's arithmetic never depends
 //     on the other rows or on the batch (a causal row equals a plain AR call
-//     at its position, bit for bit);
+//     at its position, bit for bit).  An item's chunks are shared in even
+//     runs over as many workgroups as fill the chip twice; a workgroup streams
+//     its run through one ring, two workgroups per CU where there are more
+//     than CUs (products of one under the softmax of the other), stops at the
+//     last key its rows see, and merges without a count-in when it holds the
+//     whole item.  One workgroup per chunk, one per CU, every row tile
+//     appending the window and running to its end (before -> after):
+//     8832 prefill rows 855 -> 107 us per layer, 32 sequences of 1k-4k with
+//     128 rows each 132 -> 78, 8 of 1.1k-2.1k with 1088 rows each 205 -> 82,
+//     with 128 rows 29 -> 25, with 4 rows (AR) 22 -> 21;
 //   * balanced (chunk_keys == 0): the items' tiles are concatenated and every
 //     workgroup takes an equal contiguous share, so the grid finishes together
 //     whatever the length mix; only shares that split an item publish
@@ -47,6 +56,7 @@
 // fp32 path: a plain per-(sequence, row, head) workgroup, fp32 throughout.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "dvs_common.h"
@@ -54,7 +64,7 @@
 namespace dvs {
 
 constexpr int KT = 64;                 // keys per tile
-constexpr int NSTAGE = 4;              // LDS ring depth for cache tiles
+constexpr int NSTAGE = 4;              // LDS ring depth of the balanced split
 constexpr int SUB_TILES = 256;         // tiles whose page ids are staged at once
 constexpr int MAX_CHUNK_KEYS = 16384;
 constexpr int BAL_MAX_SEGS = 16;       // balanced mode: segments per item (bound)
@@ -89,7 +99,8 @@ struct AttnParams {
   int rows_total, n_row_tiles, n_items;
   int balanced;      // 0: aligned chunks, 1: balanced shares
   int chunk_tiles;   // aligned: tiles per chunk
-  int n_chunks_max;  // aligned: grid rows
+  int wgs_per_item;  // aligned: workgroups an item's chunks are shared over
+  int appended;      // the window's K/V are in the pool already
   int share_min;     // balanced: minimum tiles per workgroup
   int max_segs;      // partial slots per item
   int group;         // mask rows per group (0: one block of n_mask rows)
@@ -165,7 +176,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 }
 
 // Wait until at most `tiles_after` cache tiles (NPL loads per lane each) are
-// still in flight (tiles_after in [0, NSTAGE - 2]).  A bound above 63 is
+// still in flight.  A bound above 63 is
 // clamped, which only waits longer.
 template <int N>
 __device__ __forceinline__ void wait_vmcnt_clamped() {
@@ -174,9 +185,9 @@ __device__ __forceinline__ void wait_vmcnt_clamped() {
 
 template <int NPL>
 __device__ __forceinline__ void wait_tiles(int tiles_after) {
-  static_assert(NSTAGE >= 2 && NSTAGE <= 4, "wait_tiles covers up to 2 tiles in flight");
-  if (NSTAGE >= 4 && tiles_after >= 2) wait_vmcnt_clamped<2 * NPL>();
-  else if (NSTAGE >= 3 && tiles_after >= 1) wait_vmcnt_clamped<NPL>();
+  if (tiles_after >= 3) wait_vmcnt_clamped<3 * NPL>();
+  else if (tiles_after == 2) wait_vmcnt_clamped<2 * NPL>();
+  else if (tiles_after == 1) wait_vmcnt_clamped<NPL>();
   else wait_vmcnt<0>();
 }
 
@@ -324,8 +335,10 @@ __device__ __forceinline__ void pc_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
-template <int D, int NW>
-__global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
+// NST: ring stages; rings of at most 72 KB leave room for two workgroups per
+// CU (PER_CU = 2).
+template <int D, int NW, bool BAL, int NST, int PER_CU>
+__global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p) {
   constexpr int NT = NW * 64;
   constexpr int CPR = D / 8;
   constexpr int KROWB = D * 2;
@@ -348,9 +361,10 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
   static_assert(PAGE_K % 1024 == 0 && PAGE_V % 1024 == 0, "page / segment mismatch");
   constexpr int NREG = DG * 16;
 
-  __shared__ __attribute__((aligned(1024))) char smem[NSTAGE * STAGE_B];
+  static_assert(NST >= 2 && NST <= 4, "ring stages");
+  __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_B];
   __shared__ int s_pages[SUB_TILES * 4 + 4];
-  __shared__ int s_seq[BAL_MAX_SEQS + 1];   // balanced: tile prefix over sequences
+  __shared__ int s_seq[BAL ? BAL_MAX_SEQS + 1 : 1];   // balanced: tile prefix over sequences
   __shared__ int s_flag[2];
 
   const int tid = threadIdx.x;
@@ -399,8 +413,8 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
   // segments: (item, tile range [j0, j1), segment index k, segments nseg)
   int u = 0, u_end = 0;          // balanced: global tile range of this workgroup
   int share = 0;
-  int it_a = 0, c_a = 0;         // aligned: item and chunk
-  if (p.balanced) {
+  int it_a = 0, w_a = 0;         // aligned: item and workgroup of the item
+  if constexpr (BAL) {
     // tile prefix over sequences (invalid sequences contribute no tiles)
     if (tid == 0) s_flag[0] = 0;
     for (int s0 = 0; s0 < p.S; s0 += NT) {
@@ -437,16 +451,21 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
     u_end = min(u + share, U);
     if (u >= u_end) return;
   } else {
-    int idx = blockIdx.x;
-    it_a = idx % p.n_items;
-    c_a = idx / p.n_items;
+    // the row tiles of a KV head share its cache: each XCD (blockIdx mod 8)
+    // takes a contiguous run of items, the last row tiles (which see the most
+    // keys) first
+    const int per = (p.n_items + 7) / 8;
+    const int q8 = (int)blockIdx.x >> 3;
+    w_a = q8 / per;
+    it_a = ((int)blockIdx.x & 7) * per + q8 % per;
+    if (it_a >= p.n_items) return;
   }
 
   bool first_segment = true;
   int s_cur = 0;                 // balanced: sequence cursor
   while (true) {
-    int s, kvh, rt, it, j0, j1, k, nseg, L;
-    if (p.balanced) {
+    int s, kvh, rt, it, j0, j1, k, nseg, L, nwg;
+    if constexpr (BAL) {
       if (u >= u_end) break;
       while (s_seq[s_cur + 1] * HN <= u) ++s_cur;
       s = s_cur;
@@ -462,26 +481,35 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
       const int P0 = s_seq[s] * HN + qi * tiles;     // first unit of the item
       k = (int)blockIdx.x - P0 / share;
       nseg = (P0 + tiles - 1) / share - P0 / share + 1;
+      nwg = nseg;
       u += j1 - j0;
     } else {
       if (!first_segment) break;
-      it = it_a;
-      s = it / HN;
-      const int qi = it - s * HN;
+      s = it_a / HN;
+      const int qi = it_a - s * HN;
       kvh = qi / p.n_row_tiles;
-      rt = qi - kvh * p.n_row_tiles;
+      rt = p.n_row_tiles - 1 - (qi - kvh * p.n_row_tiles);
+      it = s * HN + kvh * p.n_row_tiles + rt;
       L = p.kv_len[s];
       const int T = L + R;
       if (L < 0 || T > p.max_pages * 16) {
-        if (c_a == 0 && qi == 0 && tid == 0) set_err(p.err, DVS_ERR_MAX_PAGES);
+        if (w_a == 0 && qi == 0 && tid == 0) set_err(p.err, DVS_ERR_MAX_PAGES);
         return;
       }
-      const int tiles = (T + KT - 1) / KT;
+      // the keys that some row of the tile sees (the limits grow with the
+      // row); what lies past them would only add zero weights
+      const int r_last = min((rt + 1) * RPW, p.rows_total) - 1;
+      const int rl = r_last / p.G;
+      const int seen = max(row_hi(p, L, rl), group_interval(p, L, rl).hi2) + 1;
+      const int tiles = (seen + KT - 1) / KT;
       nseg = (tiles + p.chunk_tiles - 1) / p.chunk_tiles;
-      if (c_a >= nseg) return;
-      k = c_a;
-      j0 = c_a * p.chunk_tiles;
-      j1 = min(tiles, j0 + p.chunk_tiles);
+      // the item's chunks in even runs over its workgroups
+      const int run = (nseg + p.wgs_per_item - 1) / p.wgs_per_item;
+      nwg = (nseg + run - 1) / run;
+      if (w_a >= nwg) return;
+      k = w_a * run;
+      j0 = k * p.chunk_tiles;
+      j1 = min(tiles, (k + run) * p.chunk_tiles);
     }
     if (!first_segment) __syncthreads();   // previous segment fully done with LDS
     first_segment = false;
@@ -621,40 +649,85 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
     };
 
     // ---- the window keys of the segment's tiles go to their pool slots
-    // first; then every tile streams through the direct-load ring
-    {
-      const int wa = max(L, j0 * KT), wb = min(T, j1 * KT);
-      if (wa < wb) {
-        append_window<D, NT>(tid, wa, wb, L, s, R, p.Hkv, kvh, pt, p.pool_pages, kpb, vpb, knb, vnb);
-        wait_vmcnt<0>();
-        __syncthreads();
+    // before their tiles stream in; unless a launch of its own has appended
+    // them (aligned chunks of several row tiles)
+    const int wa = max(L, j0 * KT), wb = min(T, j1 * KT);
+    bool append = wa < wb && !p.appended;
+
+    // ---- end of a segment (aligned: of each chunk): the output if the item
+    // has no other, else its partial
+    auto write_out = [&](const f32x16* ov, float inv) {
+      if (!rvalid) return;
+      __bf16* orow = out + (((size_t)s * R + r) * p.Hq + h) * D;
+#pragma unroll
+      for (int dg = 0; dg < DG; ++dg)
+#pragma unroll
+        for (int g4 = 0; g4 < 4; ++g4) {
+          const int d = dg * 32 + 8 * g4 + 4 * hh;
+          const f32x2 v01 = f32x2{ov[dg][4 * g4 + 0] * inv, ov[dg][4 * g4 + 1] * inv};
+          const f32x2 v23 = f32x2{ov[dg][4 * g4 + 2] * inv, ov[dg][4 * g4 + 3] * inv};
+          const uint32_t w0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2));
+          const uint32_t w1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2));
+          *(u32x2*)(orow + d) = u32x2{w0, w1};
+        }
+    };
+    const int wg0 = BAL ? (int)blockIdx.x - k : 0;
+    // a wave whose 32 rows all lie past the item's rows has nothing to
+    // compute, publish or merge (few-row calls run four waves for the copies)
+    const bool wave_rows = rt * RPW + w * 32 < p.rows_total;
+    constexpr int NWD = NREG / 8;   // 16-byte words of a thread's partial
+    auto finish = [&]() {
+      {
+        const f32x2 hp = halves_pair(lsum);
+        lsum = hp[0] + hp[1];
       }
-    }
+      const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
+      if (nseg == 1) {
+        write_out(o, inv);
+        return;
+      }
+      // Publish the partial: O / l in bf16 (16-byte words of 8 values, word j
+      // of every thread side by side, so that each store and load of a wave
+      // covers 1 KB in one piece) and (m, l) in fp32 per thread.
+      if (!wave_rows) return;
+      const size_t slot = part_slot(BAL, it, p.max_segs, wg0, k);
+      uint32_t* po = (uint32_t*)p.part_o + slot * (size_t)(NT * NREG / 2) + (size_t)tid * 4;
+      float* pml = p.part_ml + slot * (size_t)(NT * 2) + (size_t)tid * 2;
+      *(f32x2*)pml = f32x2{m, lsum};
+#pragma unroll
+      for (int jw = 0; jw < NWD; ++jw) {
+        u32x4 v;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int f0 = 8 * jw + 2 * e;   // element f of the thread: o[f / 16][f % 16]
+          const f32x2 pr = f32x2{o[f0 / 16][f0 % 16] * inv, o[(f0 + 1) / 16][(f0 + 1) % 16] * inv};
+          v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
+        }
+        *(u32x4*)(po + jw * (NT * 4)) = v;
+      }
+    };
     // ---- the segment's tiles, in sub-ranges whose page ids fit in LDS
     for (int ja = j0; ja < j1; ja += SUB_TILES) {
       const int jb = min(j1, ja + SUB_TILES);
       const int pg_lo = ja * 4;
       const int pg_hi = jb * 4;
       if (ja != j0) __syncthreads();
-      if (tid == 0) s_flag[1] = 0;
-      __syncthreads();
       for (int i = tid; i < pg_hi - pg_lo; i += NT) {
         // pages past the last one of the sequence (in the tile that runs
         // past T) repeat the last page: their keys are masked
         int pg = (ja == j0 && i == tid) ? pg_pre : pt[min(pg_lo + i, n_valid - 1)];
         if (pg < 0 || pg >= p.pool_pages) {
           pg = 0;
-          s_flag[1] = 1;
+          set_err(p.err, DVS_ERR_BAD_PAGE);
         }
         s_pages[i] = pg;
       }
-      __syncthreads();   // also completes the Q loads
-      if (tid == 0 && s_flag[1]) set_err(p.err, DVS_ERR_BAD_PAGE);
+      __syncthreads();
 
       // every tile through the direct-load ring; tiles that reach L are masked
       const int n_main = jb - ja;
       auto issue = [&](int i) {
-        char* stage = smem + (i % NSTAGE) * STAGE_B;
+        char* stage = smem + (i % NST) * STAGE_B;
         const int pbase = i * 4;          // first page of tile ja+i, relative to pg_lo
 #pragma unroll
         for (int j = 0; j < K_INS; ++j) {
@@ -673,68 +746,54 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
               (__attribute__((address_space(3))) void*)(stage + KTILE_B + seg * 1024), 16, 0, 0);
         }
       };
-#pragma unroll
-      for (int i = 0; i < NSTAGE - 1; ++i)
-        if (i < n_main) issue(i);
+      // the whole ring is filled; from then on slot i - 1 is refilled once
+      // every wave is past tile i - 1
+      const int n_pre = min(NST, n_main);
+      int i0 = 0;
+      if (append) {
+        // the tiles below L go out first, the append under their copies
+        append = false;
+        const int n_c = min(n_pre, max(0, L / KT - ja));
+        for (; i0 < n_c; ++i0) issue(i0);
+        append_window<D, NT>(tid, wa, wb, L, s, R, p.Hkv, kvh, pt, p.pool_pages, kpb, vpb, knb, vnb);
+        wait_vmcnt<0>();
+        __syncthreads();
+      }
+      for (; i0 < n_pre; ++i0) issue(i0);
+      int left = BAL ? 0 : p.chunk_tiles - (ja - j0) % p.chunk_tiles;   // tiles left in the chunk
       for (int i = 0; i < n_main; ++i) {
-        wait_tiles<NPL>(min(NSTAGE - 2, n_main - 1 - i));
+        wait_tiles<NPL>(min(i == 0 ? NST - 1 : NST - 2, n_main - 1 - i));
         __builtin_amdgcn_s_barrier();     // tile i complete for every wave; tile i-1 consumed
-        if (i + NSTAGE - 1 < n_main) issue(i + NSTAGE - 1);
-        compute_tile(smem + (i % NSTAGE) * STAGE_B, (ja + i) * KT, ja + i >= L / KT);
+        if (i > 0 && i + NST - 1 < n_main) issue(i + NST - 1);
+        const int j = ja + i;
+        const bool masked = j >= L / KT;
+        bool live = wave_rows;
+        if (masked && live) {
+          // a tile that none of the wave's rows sees leaves m, l and O as
+          // they are
+          const Vis2 v2 = rvalid ? group_interval(p, L, r) : Vis2{1 << 30, -1};
+          live = __any(j * KT <= hi || (j * KT <= v2.hi2 && j * KT + KT - 1 >= v2.lo2));
+        }
+        if (live) compute_tile(smem + (i % NST) * STAGE_B, j * KT, masked);
+        if constexpr (!BAL) {
+          if (--left == 0 || j + 1 == j1) {
+            finish();
+            ++k;
+            left = p.chunk_tiles;
+#pragma unroll
+            for (int dg = 0; dg < DG; ++dg) o[dg] = f32x16{};
+            m = -INFINITY;
+            lsum = 0.f;
+          }
+        }
       }
     }
-
-    // ---- finish the segment
-    {
-      const f32x2 hp = halves_pair(lsum);
-      lsum = hp[0] + hp[1];
-    }
-    auto write_out = [&](const f32x16* ov, float inv) {
-      if (!rvalid) return;
-      __bf16* orow = out + (((size_t)s * R + r) * p.Hq + h) * D;
-#pragma unroll
-      for (int dg = 0; dg < DG; ++dg)
-#pragma unroll
-        for (int g4 = 0; g4 < 4; ++g4) {
-          const int d = dg * 32 + 8 * g4 + 4 * hh;
-          const f32x2 v01 = f32x2{ov[dg][4 * g4 + 0] * inv, ov[dg][4 * g4 + 1] * inv};
-          const f32x2 v23 = f32x2{ov[dg][4 * g4 + 2] * inv, ov[dg][4 * g4 + 3] * inv};
-          const uint32_t w0 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2));
-          const uint32_t w1 = __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2));
-          *(u32x2*)(orow + d) = u32x2{w0, w1};
-        }
-    };
-    if (nseg == 1) {
-      write_out(o, lsum > 0.f ? 1.f / lsum : 0.f);
-      continue;
-    }
-    // Publish the partial: O / l in bf16 (16-byte words of 8 values, word j
-    // of every thread side by side, so that each store and load of a wave
-    // covers 1 KB in one piece) and (m, l) in fp32 per thread; wait for the
-    // stores, then count in; the workgroup that completes the item merges.
-    const int wg0 = (int)blockIdx.x - k;
-    const size_t slot = part_slot(p.balanced, it, p.max_segs, wg0, k);
-    // a wave whose 32 rows all lie past the item's rows has nothing to
-    // publish or merge (few-row calls run four waves for the copies)
-    const bool wave_rows = rt * RPW + w * 32 < p.rows_total;
-    constexpr int NWD = NREG / 8;   // 16-byte words of a thread's partial
-    if (wave_rows) {
-      uint32_t* po = (uint32_t*)p.part_o + slot * (size_t)(NT * NREG / 2) + (size_t)tid * 4;
-      float* pml = p.part_ml + slot * (size_t)(NT * 2) + (size_t)tid * 2;
-      *(f32x2*)pml = f32x2{m, lsum};
-      const float inv = lsum > 0.f ? 1.f / lsum : 0.f;
-#pragma unroll
-      for (int jw = 0; jw < NWD; ++jw) {
-        u32x4 v;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int f0 = 8 * jw + 2 * e;   // element f of the thread: o[f / 16][f % 16]
-          const f32x2 pr = f32x2{o[f0 / 16][f0 % 16] * inv, o[(f0 + 1) / 16][(f0 + 1) % 16] * inv};
-          v[e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(pr, bf16x2));
-        }
-        *(u32x4*)(po + jw * (NT * 4)) = v;
-      }
-    }
+    if constexpr (BAL) finish();
+    if (nseg == 1) continue;
+    // A workgroup that holds the whole item merges its own partials: every
+    // thread reads back what it wrote.  Otherwise wait for the stores, then
+    // count in; the workgroup that completes the item merges.
+    if (nwg > 1) {
     wait_vmcnt<0>();
     __syncthreads();
     // The count-in is a release (the partials written by every thread of the
@@ -745,18 +804,19 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
     // to all its threads).  Only that workgroup pays for the acquire.
     if (tid == 0) {
       const bool last = __hip_atomic_fetch_add(&p.counters[it], 1, __ATOMIC_RELEASE,
-                                               __HIP_MEMORY_SCOPE_AGENT) == nseg - 1;
+                                               __HIP_MEMORY_SCOPE_AGENT) == nwg - 1;
       if (last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       s_flag[0] = last;
     }
     __syncthreads();
     if (!s_flag[0]) continue;
     if (tid == 0) __hip_atomic_store(&p.counters[it], 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (!wave_rows) continue;
     // Partials are read in batches issued in full before any of it is used,
     // so the loads overlap instead of each one waiting for the previous.
     auto ml_of = [&](int c) {
-      return *(const f32x2*)(p.part_ml + part_slot(p.balanced, it, p.max_segs, wg0, c) * (NT * 2) +
+      return *(const f32x2*)(p.part_ml + part_slot(BAL, it, p.max_segs, wg0, c) * (NT * 2) +
                              (size_t)tid * 2);
     };
     // SB segments per batch (eight where the registers allow), added in
@@ -764,7 +824,7 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
     // M, the largest m_c, is found in a first pass over the (m, l) pairs,
     // or from the batch itself when one batch holds every segment (one
     // round of loads instead of two).
-    constexpr int SB = NREG <= 48 ? 8 : 4;
+    constexpr int SB = (NREG <= 48 ? 8 : 4) / PER_CU;
     float M = -INFINITY;
     if (nseg > SB) {
       for (int c0 = 0; c0 < nseg; c0 += 8) {
@@ -787,7 +847,7 @@ __global__ void __launch_bounds__(NW * 64, 1) attn_bf16_kernel(AttnParams p) {
       for (int b = 0; b < SB; ++b) {
         const int c = min(c0 + b, nseg - 1);
         const uint32_t* src = (const uint32_t*)p.part_o +
-                              part_slot(p.balanced, it, p.max_segs, wg0, c) * (NT * NREG / 2) +
+                              part_slot(BAL, it, p.max_segs, wg0, c) * (NT * NREG / 2) +
                               (size_t)tid * 4;
 #pragma unroll
         for (int jw = 0; jw < NWD; ++jw) pv[b][jw] = *(const u32x4*)(src + jw * (NT * 4));
@@ -1660,9 +1720,26 @@ __global__ void attn_zero_kernel(int32_t* __restrict__ p, int n) {
   if (i < n) p[i] = 0;
 }
 
+// Appends the window's K/V ([L, T)) to the pool, one workgroup per (64-key
+// tile, KV head, sequence): aligned calls of several row tiles, whose
+// workgroups would otherwise each append the whole window again (8832 rows,
+// 18 window tiles, 35 row tiles of 4 KV heads: most of the launch's time).
+template <int D>
+__global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
+  const int s = blockIdx.z, kvh = blockIdx.y;
+  const int L = p.kv_len[s], T = L + p.R;
+  if (L < 0 || T > p.max_pages * 16) return;   // reported by the attention launch
+  const int j = L / KT + (int)blockIdx.x;
+  const int a = max(L, j * KT), b = min(T, (j + 1) * KT);
+  if (a >= b) return;
+  append_window<D, 256>(threadIdx.x, a, b, L, s, p.R, p.Hkv, kvh, p.page_table + (size_t)s * p.max_pages,
+                        p.pool_pages, (char*)p.k_pool, (char*)p.v_pool, (const char*)p.k_new,
+                        (const char*)p.v_new);
+}
+
 struct AttnPlan {
   int nw, rows_total, rows_per_wg, n_row_tiles, n_items, balanced, pc;
-  int chunk_tiles, n_chunks_max, share_min, max_segs, grid;
+  int chunk_tiles, n_chunks_max, wgs_per_item, per_cu, share_min, max_segs, grid;
   size_t off_counters, off_ml, off_o, bytes;
 };
 
@@ -1683,10 +1760,10 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     // (8 waves, one producer and one consumer per SIMD) over 256 rows
     pl.pc = (pl.balanced && pl.rows_total > 128) ? 1 : 0;
     if (pl.pc) pl.nw = 8;
-    // aligned chunks with few rows (decode steps): four waves all the same,
-    // so that a chunk's copies are spread over them (a row's arithmetic does
-    // not depend on the wave count)
-    if (!pl.balanced && pl.nw < 4) pl.nw = 4;
+    // aligned chunks: four waves whatever the rows, so that a decode step's
+    // copies are spread over them and two workgroups fit a CU (a row's
+    // arithmetic does not depend on the wave count)
+    if (!pl.balanced) pl.nw = 4;
   } else {
     pl.nw = 4;
   }
@@ -1712,7 +1789,14 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     pl.chunk_tiles = C / KT;
     pl.n_chunks_max = (max_tiles + pl.chunk_tiles - 1) / pl.chunk_tiles;
     pl.max_segs = pl.n_chunks_max;
-    pl.grid = pl.n_chunks_max * pl.n_items;
+    // An item's chunks are shared over enough workgroups for two per CU, one
+    // chunk each at the least: fewer leave CUs idle, more repeat the prologue
+    // and the count-in (32 sequences of 1k-4k cached tokens, four layers of a
+    // fused step: 1.14 / 1.09 / 1.15 / 1.15 ms with 1 / 2 / 3 / 4 per CU).
+    const int want = 2 * device_cus();
+    pl.wgs_per_item = std::min(pl.n_chunks_max, (want + pl.n_items - 1) / pl.n_items);
+    pl.per_cu = (long long)pl.wgs_per_item * pl.n_items > device_cus() ? 2 : 1;
+    pl.grid = pl.wgs_per_item * ((pl.n_items + 7) / 8 * 8);
   }
   const int NT = pl.nw * 64;
   // partial slots: two per workgroup in the balanced split, one per (item,
@@ -1726,7 +1810,9 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     const size_t o_b = pl.pc ? (size_t)256 * (2 * (D / 32) * 16) * 2
                              : (size_t)NT * (D / 32) * 16 * 2;
     pl.off_counters = 0;
-    pl.off_ml = align256((size_t)pl.n_items * sizeof(int32_t));
+    // (no counters where one workgroup holds every chunk of its item)
+    const bool counted = pl.balanced || pl.wgs_per_item > 1;
+    pl.off_ml = counted ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0;
     pl.off_o = pl.off_ml + align256(slots * ml_b);
     pl.bytes = pl.off_o + align256(slots * o_b);
   } else {
@@ -1736,19 +1822,29 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
 }
 
 template <int D>
-static void launch_bf16(const AttnPlan& pl, const AttnParams& prm, hipStream_t st) {
-  if (pl.pc) {
-    hipLaunchKernelGGL((attn_bf16_pc_kernel<D, 4>), dim3(pl.grid), dim3(512), 0, st, prm);
+static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
+  const dim3 gr(pl.grid);
+  if (!pl.balanced) {
+    // ring stages: what one or two workgroups per CU leave room for
+    constexpr int NST2 = D == 128 ? 2 : (D == 96 ? 3 : 4);
+    prm.appended = pl.n_row_tiles > 1;
+    if (prm.appended)
+      hipLaunchKernelGGL(attn_append_kernel<D>, dim3((prm.R + KT - 1) / KT + 1, prm.Hkv, prm.S), dim3(256), 0, st, prm);
+    if (pl.per_cu == 2 || NST2 == 4)
+      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, prm);
+    else
+      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, prm);
     return;
   }
+  if (pl.pc) {
+    hipLaunchKernelGGL((attn_bf16_pc_kernel<D, 4>), gr, dim3(512), 0, st, prm);
+    return;
+  }
+  // (more than 128 rows take the producer/consumer kernel)
   switch (pl.nw) {
-    case 8:
-      if constexpr (D != 96)
-        hipLaunchKernelGGL((attn_bf16_kernel<D, 8>), dim3(pl.grid), dim3(512), 0, st, prm);
-      break;
-    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4>), dim3(pl.grid), dim3(256), 0, st, prm); break;
-    case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2>), dim3(pl.grid), dim3(128), 0, st, prm); break;
-    default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1>), dim3(pl.grid), dim3(64), 0, st, prm); break;
+    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, NSTAGE, 1>), gr, dim3(256), 0, st, prm); break;
+    case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, prm); break;
+    default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1, true, NSTAGE, 1>), gr, dim3(64), 0, st, prm); break;
   }
 }
 
@@ -1819,7 +1915,7 @@ static int attn_launch(const void* q, const void* k_new, const void* v_new, void
   prm.Hkv = Hkv; prm.G = Hq / Hkv; prm.max_pages = max_pages; prm.pool_pages = num_pool_pages;
   prm.rows_total = pl.rows_total; prm.n_row_tiles = pl.n_row_tiles; prm.n_items = pl.n_items;
   prm.balanced = pl.balanced; prm.chunk_tiles = pl.chunk_tiles;
-  prm.n_chunks_max = pl.n_chunks_max; prm.share_min = pl.share_min; prm.max_segs = pl.max_segs;
+  prm.wgs_per_item = pl.wgs_per_item; prm.share_min = pl.share_min; prm.max_segs = pl.max_segs;
   prm.group = n_groups > 1 ? mask_group : 0;
   prm.n_groups = n_groups;
   prm.scale = softmax_scale;
@@ -1834,7 +1930,7 @@ static int attn_launch(const void* q, const void* k_new, const void* v_new, void
     if (scratch_cap > 0) {
       // the array keeps the previous call's contents: clear the counters
       const int nw = (int)((pl.off_ml - pl.off_counters) / sizeof(int32_t));
-      hipLaunchKernelGGL(attn_zero_kernel, dim3((nw + 255) / 256), dim3(256), 0, st, prm.counters, nw);
+      if (nw) hipLaunchKernelGGL(attn_zero_kernel, dim3((nw + 255) / 256), dim3(256), 0, st, prm.counters, nw);
     }
     if (D == 128) launch_bf16<128>(pl, prm, st);
     else if (D == 96) launch_bf16<96>(pl, prm, st);

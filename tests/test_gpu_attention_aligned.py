@@ -1,0 +1,59 @@
+"""GPU: aligned attention chunks shared over workgroups.  An item's chunks run
+in one workgroup or in many, the window is appended by the attention launch
+(one row tile) or by one of its own (several), and chunks past the keys a row
+tile sees are skipped: against the oracle, and every sequence of a batch bit
+for bit against the same sequence alone (which splits its chunks otherwise)."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import attention as oa
+from paper_2609_26638_amd import dvs, synth
+from tests.gpu_util import dev_attn, max_rel_err, to_f64
+
+pytestmark = pytest.mark.gpu
+
+
+def _call(d, s, nc, nm, group, scale, chunk):
+    sl = slice(s, s + 1) if s is not None else slice(None)
+    err = torch.zeros(1, dtype=torch.int32, device="cuda")
+    kp, vp = d["k_pool"].clone(), d["v_pool"].clone()
+    out = dvs.attn_hybrid_block_grouped(d["q"][sl], d["k_new"][sl], d["v_new"][sl], kp, vp,
+                                        d["page_table"][sl], d["kv_len"][sl], nc, nm, group, scale,
+                                        err=err, chunk_keys=chunk)
+    assert int(err.item()) == 0
+    return out, kp, vp
+
+
+# (lens, causal, mask, group, heads, kv heads, head dim, chunk): a prefill (no
+# cache, many row tiles, each seeing its own prefix); a batch of many items
+# (runs of several chunks per workgroup) whose row tiles end inside a wave; one
+# row tile with a window over a chunk's edge; mask groups that skip the tiles
+# of the groups before; one AR row at the edges of tiles and chunks.
+@pytest.mark.parametrize("lens,nc,nm,group,Hq,Hkv,D,chunk", [
+    ([0, 0], 397, 7, 0, 8, 2, 96, 128),
+    ([700, 65, 1023, 0, 311, 64, 900, 128] * 6, 33, 7, 0, 16, 4, 64, 64),
+    ([250, 255, 256, 640, 63], 13, 13, 0, 8, 2, 128, 256),
+    ([500, 190], 8, 64, 8, 16, 4, 96, 128),
+    ([500, 190, 3], 12, 144, 12, 8, 2, 128, 64),
+    ([0, 63, 64, 255, 256, 1500], 1, 0, 0, 4, 1, 96, 256),
+])
+def test_aligned_chunks(lens, nc, nm, group, Hq, Hkv, D, chunk):
+    S = len(lens)
+    ai = synth.make_attn_inputs(3, S, lens, nc, nm, Hq, Hkv, D, "bf16", std=1.0, scatter=True)
+    d = dev_attn(ai)
+    out, kp, vp = _call(d, None, nc, nm, group, ai.scale, chunk)
+    for s in sorted({0, 1, S - 1}):
+        one, _, _ = _call(d, s, nc, nm, group, ai.scale, chunk)
+        assert torch.equal(one[0], out[s]), s
+    n = min(S, 4)
+    k_ref, v_ref = ai.as_f64("k_pool"), ai.as_f64("v_pool")
+    ref = oa.attn_hybrid_block(ai.as_f64("q")[:n], ai.as_f64("k_new")[:n], ai.as_f64("v_new")[:n],
+                               k_ref, v_ref, ai.state.page_table[:n], ai.state.kv_len[:n], nc, nm,
+                               ai.scale, group=group)
+    assert max_rel_err(to_f64(out[:n]), ref) <= 2e-2
+    # the window reached its slots and nothing else changed
+    for s in range(n):
+        held = ai.state.page_table[s][:(lens[s] + nc + nm + 15) // 16]
+        np.testing.assert_array_equal(to_f64(kp)[held], k_ref[held])
+        np.testing.assert_array_equal(to_f64(vp)[held], v_ref[held])
