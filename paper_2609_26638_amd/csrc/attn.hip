@@ -100,6 +100,7 @@ struct AttnParams {
   int balanced;      // 0: aligned chunks, 1: balanced shares
   int chunk_tiles;   // aligned: tiles per chunk
   int wgs_per_item;  // aligned: workgroups an item's chunks are shared over
+  int xcd_run;       // aligned: items of a contiguous run per XCD (0: dealt out in turn)
   int appended;      // the window's K/V are in the pool already
   int share_min;     // balanced: minimum tiles per workgroup
   int max_segs;      // partial slots per item
@@ -335,6 +336,47 @@ __device__ __forceinline__ void pc_barrier() {
   asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// Balanced split: s_seq[s] = sum of units(L) over the sequences before s, for
+// s = 0 .. S, and the lengths (invalid sequences have no units).  One wave
+// scan and one round over the waves' totals per NT sequences.
+template <int NT, typename F>
+__device__ __forceinline__ void seq_prefix(const AttnParams& p, int tid, int* s_seq, int* s_len, int* s_tot,
+                                           F&& units) {
+  const int lane = tid & 63;
+  int carry = 0;
+  for (int s0 = 0; s0 < p.S; s0 += NT) {
+    const int s = s0 + tid;
+    int t = 0;
+    if (s < p.S) {
+      const int L = p.kv_len[s];
+      s_len[s] = L;
+      if (L < 0 || L + p.R > p.max_pages * 16) {
+        if (blockIdx.x == 0) set_err(p.err, DVS_ERR_MAX_PAGES);
+      } else {
+        t = units(L);
+      }
+    }
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(t, off);
+      if (lane >= off) t += v;
+    }
+    if (s0) __syncthreads();   // the previous round's totals are read
+    if (lane == 63) s_tot[tid >> 6] = t;
+    __syncthreads();
+    int before = carry;
+#pragma unroll
+    for (int w = 0; w < NT / 64; ++w) {
+      const int v = s_tot[w];
+      if (w < (tid >> 6)) before += v;
+      carry += v;
+    }
+    if (s < p.S) s_seq[1 + s] = before + t;
+  }
+  if (tid == 0) s_seq[0] = 0;
+  __syncthreads();
+}
+
 // NST: ring stages; rings of at most 72 KB leave room for two workgroups per
 // CU (PER_CU = 2).
 template <int D, int NW, bool BAL, int NST, int PER_CU>
@@ -365,7 +407,8 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
   __shared__ __attribute__((aligned(1024))) char smem[NST * STAGE_B];
   __shared__ int s_pages[SUB_TILES * 4 + 4];
   __shared__ int s_seq[BAL ? BAL_MAX_SEQS + 1 : 1];   // balanced: tile prefix over sequences
-  __shared__ int s_flag[2];
+  __shared__ int s_len[BAL ? BAL_MAX_SEQS : 1];       // balanced: the lengths
+  __shared__ int s_flag[NW];
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
@@ -415,36 +458,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
   int share = 0;
   int it_a = 0, w_a = 0;         // aligned: item and workgroup of the item
   if constexpr (BAL) {
-    // tile prefix over sequences (invalid sequences contribute no tiles)
-    if (tid == 0) s_flag[0] = 0;
-    for (int s0 = 0; s0 < p.S; s0 += NT) {
-      __syncthreads();
-      int t = 0;
-      const int s = s0 + tid;
-      if (s < p.S) {
-        const int L = p.kv_len[s];
-        const int T = L + R;
-        if (L < 0 || T > p.max_pages * 16) {
-          s_flag[0] = 1;
-        } else {
-          t = (T + KT - 1) / KT;
-        }
-      }
-      // inclusive scan of t over this block of sequences (Hillis-Steele)
-      s_seq[1 + tid + s0] = t;   // s0 + NT <= BAL_MAX_SEQS guaranteed by the host
-      __syncthreads();
-      for (int off = 1; off < NT; off <<= 1) {
-        const int v = (tid >= off && s0 + tid < p.S) ? s_seq[1 + s0 + tid - off] : 0;
-        __syncthreads();
-        if (s0 + tid < p.S) s_seq[1 + s0 + tid] += v;
-        __syncthreads();
-      }
-      if (s0 > 0 && s0 + tid < p.S) s_seq[1 + s0 + tid] += s_seq[s0];
-      // (the carry read above sees the previous block's final value)
-    }
-    if (tid == 0) s_seq[0] = 0;
-    __syncthreads();
-    if (blockIdx.x == 0 && tid == 0 && s_flag[0]) set_err(p.err, DVS_ERR_MAX_PAGES);
+    seq_prefix<NT>(p, tid, s_seq, s_len, s_flag, [&](int L) { return (L + R + KT - 1) / KT; });
     const int U = s_seq[p.S] * HN;
     share = max((U + (int)gridDim.x - 1) / (int)gridDim.x, p.share_min);
     u = (int)blockIdx.x * share;
@@ -452,13 +466,18 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
     if (u >= u_end) return;
   } else {
     // the row tiles of a KV head share its cache: each XCD (blockIdx mod 8)
-    // takes a contiguous run of items, the last row tiles (which see the most
-    // keys) first
-    const int per = (p.n_items + 7) / 8;
-    const int q8 = (int)blockIdx.x >> 3;
-    w_a = q8 / per;
-    it_a = ((int)blockIdx.x & 7) * per + q8 % per;
-    if (it_a >= p.n_items) return;
+    // takes a contiguous run of items.  Few items are dealt out in turn, so
+    // that every XCD streams (4 items on 4 XCDs: 28.1 against 26.1 us).
+    const int per = p.xcd_run;
+    if (per) {
+      const int q8 = (int)blockIdx.x >> 3;
+      w_a = q8 / per;
+      it_a = ((int)blockIdx.x & 7) * per + q8 % per;
+      if (it_a >= p.n_items) return;
+    } else {
+      it_a = (int)blockIdx.x % p.n_items;
+      w_a = (int)blockIdx.x / p.n_items;
+    }
   }
 
   bool first_segment = true;
@@ -469,7 +488,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
       if (u >= u_end) break;
       while (s_seq[s_cur + 1] * HN <= u) ++s_cur;
       s = s_cur;
-      L = p.kv_len[s];
+      L = s_len[s];
       const int tiles = s_seq[s + 1] - s_seq[s];
       const int local = u - s_seq[s] * HN;
       const int qi = local / tiles;
@@ -488,7 +507,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
       s = it_a / HN;
       const int qi = it_a - s * HN;
       kvh = qi / p.n_row_tiles;
-      rt = p.n_row_tiles - 1 - (qi - kvh * p.n_row_tiles);
+      rt = p.n_row_tiles - 1 - (qi - kvh * p.n_row_tiles);   // the last rows see the most keys: first
       it = s * HN + kvh * p.n_row_tiles + rt;
       L = p.kv_len[s];
       const int T = L + R;
@@ -946,7 +965,8 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
   __shared__ int s_resc[NP];
   __shared__ int s_pages[SUB_TILES * 4 + 4];
   __shared__ int s_seq[BAL_MAX_SEQS + 1];
-  __shared__ int s_flag[2];
+  __shared__ int s_len[BAL_MAX_SEQS];
+  __shared__ int s_flag[NP * 2];
 
   const int tid = threadIdx.x;
   // wave-uniform role (an SGPR), so the role branch is a real branch: its
@@ -967,30 +987,9 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
   // ---- balanced split: cost-unit prefix over sequences (every item of a
   // sequence has the same tiles), equal shares of units; a tile belongs to
   // the workgroup whose share holds its first unit
-  if (tid == 0) s_flag[0] = 0;
-  for (int s0 = 0; s0 < p.S; s0 += NP * 128) {
-    __syncthreads();
-    int t = 0;
-    const int s = s0 + tid;
-    if (s < p.S) {
-      const int L = p.kv_len[s];
-      const int T = L + R;
-      if (L < 0 || T > p.max_pages * 16) s_flag[0] = 1;
-      else t = PC_WM * (L / KT) + PC_WW * ((T + KT - 1) / KT - L / KT) + PC_WE;
-    }
-    s_seq[1 + tid + s0] = t;
-    __syncthreads();
-    for (int off = 1; off < NP * 128; off <<= 1) {
-      const int v = (tid >= off && s0 + tid < p.S) ? s_seq[1 + s0 + tid - off] : 0;
-      __syncthreads();
-      if (s0 + tid < p.S) s_seq[1 + s0 + tid] += v;
-      __syncthreads();
-    }
-    if (s0 > 0 && s0 + tid < p.S) s_seq[1 + s0 + tid] += s_seq[s0];
-  }
-  if (tid == 0) s_seq[0] = 0;
-  __syncthreads();
-  if (blockIdx.x == 0 && tid == 0 && s_flag[0]) set_err(p.err, DVS_ERR_MAX_PAGES);
+  seq_prefix<NP * 128>(p, tid, s_seq, s_len, s_flag, [&](int L) {
+    return PC_WM * (L / KT) + PC_WW * ((L + R + KT - 1) / KT - L / KT) + PC_WE;
+  });
   const int U = s_seq[p.S] * HN;
   const int share = max((U + (int)gridDim.x - 1) / (int)gridDim.x, p.share_min);
   const int u0 = (int)blockIdx.x * share;
@@ -1017,7 +1016,7 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
       const int ct = tidv - NC;            // consumer thread index (consumers only)
       while (s_seq[s_cur + 1] * HN <= u) ++s_cur;
       const int s = s_cur;
-      const int L = p.kv_len[s];
+      const int L = s_len[s];
       const int iu = s_seq[s + 1] - s_seq[s];            // units of one item
       const int qi = (u - s_seq[s] * HN) / iu;
       const int P0 = s_seq[s] * HN + qi * iu;             // first unit of the item
@@ -1739,7 +1738,7 @@ __global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
 
 struct AttnPlan {
   int nw, rows_total, rows_per_wg, n_row_tiles, n_items, balanced, pc;
-  int chunk_tiles, n_chunks_max, wgs_per_item, per_cu, share_min, max_segs, grid;
+  int chunk_tiles, n_chunks_max, wgs_per_item, xcd_run, per_cu, share_min, max_segs, grid;
   size_t off_counters, off_ml, off_o, bytes;
 };
 
@@ -1783,7 +1782,12 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     }
     if (pl.share_min < 1) pl.share_min = 1;
     pl.max_segs = BAL_MAX_SEGS;
-    pl.grid = device_cus();
+    // 97 .. 128 rows (four waves): two workgroups per CU, products of one
+    // under the softmax of the other (32 sequences of 1k-8k 112.7 -> 111.5 us,
+    // one of 2048 26.7 -> 24.7 us); fewer rows are not faster for it (54 rows
+    // 27.5 against 27.7 us, 6 rows 24.3 against 27.3 us)
+    pl.per_cu = !pl.pc && pl.nw == 4 ? 2 : 1;
+    pl.grid = device_cus() * pl.per_cu;
   } else {
     int C = chunk_keys > 0 ? chunk_keys : 4096;
     pl.chunk_tiles = C / KT;
@@ -1796,7 +1800,8 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     const int want = 2 * device_cus();
     pl.wgs_per_item = std::min(pl.n_chunks_max, (want + pl.n_items - 1) / pl.n_items);
     pl.per_cu = (long long)pl.wgs_per_item * pl.n_items > device_cus() ? 2 : 1;
-    pl.grid = pl.wgs_per_item * ((pl.n_items + 7) / 8 * 8);
+    pl.xcd_run = pl.n_row_tiles > 1 && pl.n_items >= 64 ? (pl.n_items + 7) / 8 : 0;
+    pl.grid = pl.wgs_per_item * (pl.xcd_run ? 8 * pl.xcd_run : pl.n_items);
   }
   const int NT = pl.nw * 64;
   // partial slots: two per workgroup in the balanced split, one per (item,
@@ -1842,7 +1847,7 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
   }
   // (more than 128 rows take the producer/consumer kernel)
   switch (pl.nw) {
-    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, NSTAGE, 1>), gr, dim3(256), 0, st, prm); break;
+    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, D == 64 ? 4 : 2, 2>), gr, dim3(256), 0, st, prm); break;
     case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, prm); break;
     default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1, true, NSTAGE, 1>), gr, dim3(64), 0, st, prm); break;
   }
@@ -1915,7 +1920,7 @@ static int attn_launch(const void* q, const void* k_new, const void* v_new, void
   prm.Hkv = Hkv; prm.G = Hq / Hkv; prm.max_pages = max_pages; prm.pool_pages = num_pool_pages;
   prm.rows_total = pl.rows_total; prm.n_row_tiles = pl.n_row_tiles; prm.n_items = pl.n_items;
   prm.balanced = pl.balanced; prm.chunk_tiles = pl.chunk_tiles;
-  prm.wgs_per_item = pl.wgs_per_item; prm.share_min = pl.share_min; prm.max_segs = pl.max_segs;
+  prm.wgs_per_item = pl.wgs_per_item; prm.xcd_run = pl.xcd_run; prm.share_min = pl.share_min; prm.max_segs = pl.max_segs;
   prm.group = n_groups > 1 ? mask_group : 0;
   prm.n_groups = n_groups;
   prm.scale = softmax_scale;
