@@ -201,13 +201,14 @@ __device__ __forceinline__ void wait_tiles(int tiles_after) {
 // them, so the window tiles then go through the same direct loads as cache
 // tiles.  Tiles start at multiples of 64 keys, so every page belongs to one
 // tile, and workgroups of different row tiles of one item write identical
-// bytes.  Every load of a thread is issued before its stores (a pool store
+// bytes.  page_of(i) is
+// the id of logical page i.  Every load of a thread is issued before its stores (a pool store
 // could alias a pool load as far as the compiler can tell).  Slots whose page
 // id is invalid are skipped (the page staging reports them).
 // ---------------------------------------------------------------------------
-template <int D, int NT>
+template <int D, int NT, typename PG>
 __device__ __forceinline__ void append_window(int tid, int a, int b, int L, int s, int R, int Hkv,
-                                              int kvh, const int32_t* __restrict__ pt, int pool_pages,
+                                              int kvh, PG&& page_of, int pool_pages,
                                               char* __restrict__ kpb, char* __restrict__ vpb,
                                               const char* __restrict__ knb,
                                               const char* __restrict__ vnb) {
@@ -226,7 +227,7 @@ __device__ __forceinline__ void append_window(int tid, int a, int b, int L, int 
       const int i = i0 + e * NT;
       const bool live = i < nk;
       const int key = a + (live ? i / CPR : 0), cc = live ? i % CPR : 0;
-      pg[e] = live ? pt[key >> 4] : -1;
+      pg[e] = live ? page_of(key >> 4) : -1;
       x[e] = *(const u32x4*)(knb + (((size_t)s * R + (key - L)) * Hkv + kvh) * KROWB + cc * 16);
     }
 #pragma unroll
@@ -243,7 +244,7 @@ __device__ __forceinline__ void append_window(int tid, int a, int b, int L, int 
 #pragma unroll 1
   for (int i = tid; i < nv; i += NT) {
     const int pi = p0 + i / D, d = i % D;
-    const int pg = pt[pi];
+    const int pg = page_of(pi);
     if (pg < 0 || pg >= pool_pages) continue;
     char* row = vpb + ((size_t)pg * Hkv + kvh) * PAGE_V + d * 32;
     const int lo = max(a, pi * 16) - pi * 16, hi = min(b, pi * 16 + 16) - pi * 16;   // new slots [lo, hi)
@@ -380,7 +381,10 @@ __device__ __forceinline__ void seq_prefix(const AttnParams& p, int tid, int* s_
 // NST: ring stages; rings of at most 72 KB leave room for two workgroups per
 // CU (PER_CU = 2).
 template <int D, int NW, bool BAL, int NST, int PER_CU>
-__global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p) {
+__global__ void __launch_bounds__(NW * 64, PER_CU)
+attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__ page_table,
+                 const void* __restrict__ q_, int R, int G, int HN, int n_row_tiles, int n_items,
+                 int xcd_run, int max_pages, int chunk_tiles, int wgs_per_item, AttnParams p) {
   constexpr int NT = NW * 64;
   constexpr int CPR = D / 8;
   constexpr int KROWB = D * 2;
@@ -415,10 +419,8 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
   const int w = tid >> 6;
   const int hh = lane >> 5;
   const int l32 = lane & 31;
-  const int R = p.R;
-  const int HN = p.Hkv * p.n_row_tiles;   // items per sequence
 
-  const __bf16* __restrict__ q = (const __bf16*)p.q;
+  const __bf16* __restrict__ q = (const __bf16*)q_;
   const char* __restrict__ knb = (const char*)p.k_new;
   const char* __restrict__ vnb = (const char*)p.v_new;
   char* __restrict__ kpb = (char*)p.k_pool;
@@ -468,15 +470,15 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
     // the row tiles of a KV head share its cache: each XCD (blockIdx mod 8)
     // takes a contiguous run of items.  Few items are dealt out in turn, so
     // that every XCD streams (4 items on 4 XCDs: 28.1 against 26.1 us).
-    const int per = p.xcd_run;
+    const int per = xcd_run;
     if (per) {
       const int q8 = (int)blockIdx.x >> 3;
       w_a = q8 / per;
       it_a = ((int)blockIdx.x & 7) * per + q8 % per;
-      if (it_a >= p.n_items) return;
+      if (it_a >= n_items) return;
     } else {
-      it_a = (int)blockIdx.x % p.n_items;
-      w_a = (int)blockIdx.x / p.n_items;
+      it_a = (int)blockIdx.x % n_items;
+      w_a = (int)blockIdx.x / n_items;
     }
   }
 
@@ -495,8 +497,8 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
       j0 = local - qi * tiles;
       j1 = min(tiles, j0 + (u_end - u));
       it = s * HN + qi;
-      kvh = qi / p.n_row_tiles;
-      rt = qi - kvh * p.n_row_tiles;
+      kvh = qi / n_row_tiles;
+      rt = qi - kvh * n_row_tiles;
       const int P0 = s_seq[s] * HN + qi * tiles;     // first unit of the item
       k = (int)blockIdx.x - P0 / share;
       nseg = (P0 + tiles - 1) / share - P0 / share + 1;
@@ -506,34 +508,34 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
       if (!first_segment) break;
       s = it_a / HN;
       const int qi = it_a - s * HN;
-      kvh = qi / p.n_row_tiles;
-      rt = p.n_row_tiles - 1 - (qi - kvh * p.n_row_tiles);   // the last rows see the most keys: first
-      it = s * HN + kvh * p.n_row_tiles + rt;
-      L = p.kv_len[s];
+      kvh = qi / n_row_tiles;
+      rt = n_row_tiles - 1 - (qi - kvh * n_row_tiles);   // the last rows see the most keys: first
+      it = s * HN + kvh * n_row_tiles + rt;
+      L = kv_len[s];
       const int T = L + R;
-      if (L < 0 || T > p.max_pages * 16) {
+      if (L < 0 || T > max_pages * 16) {
         if (w_a == 0 && qi == 0 && tid == 0) set_err(p.err, DVS_ERR_MAX_PAGES);
         return;
       }
       // the keys that some row of the tile sees (the limits grow with the
       // row); what lies past them would only add zero weights
       const int r_last = min((rt + 1) * RPW, p.rows_total) - 1;
-      const int rl = r_last / p.G;
+      const int rl = r_last / G;
       const int seen = max(row_hi(p, L, rl), group_interval(p, L, rl).hi2) + 1;
       const int tiles = (seen + KT - 1) / KT;
-      nseg = (tiles + p.chunk_tiles - 1) / p.chunk_tiles;
+      nseg = (tiles + chunk_tiles - 1) / chunk_tiles;
       // the item's chunks in even runs over its workgroups
-      const int run = (nseg + p.wgs_per_item - 1) / p.wgs_per_item;
+      const int run = (nseg + wgs_per_item - 1) / wgs_per_item;
       nwg = (nseg + run - 1) / run;
       if (w_a >= nwg) return;
       k = w_a * run;
-      j0 = k * p.chunk_tiles;
-      j1 = min(tiles, (k + run) * p.chunk_tiles);
+      j0 = k * chunk_tiles;
+      j1 = min(tiles, (k + run) * chunk_tiles);
     }
     if (!first_segment) __syncthreads();   // previous segment fully done with LDS
     first_segment = false;
     const int T = L + R;
-    const int32_t* __restrict__ pt = p.page_table + (size_t)s * p.max_pages;
+    const int32_t* __restrict__ pt = page_table + (size_t)s * max_pages;
     const int n_valid = (T + 15) >> 4;    // pages the sequence holds
     // the page ids of the segment's first sub-range, loaded together with Q
     // (one wait for both)
@@ -543,8 +545,8 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
     // ---- rows of this lane: Q fragments (B operand), visibility limit
     const int n = rt * RPW + w * 32 + l32;
     const bool rvalid = n < p.rows_total;
-    const int r = n / p.G;
-    const int h = kvh * p.G + (n - r * p.G);
+    const int r = n / G;
+    const int h = kvh * G + (n - r * G);
     const int hi = !rvalid ? -1 : row_hi(p, L, r);
     bf16x8 qf[KS];
 #pragma unroll
@@ -736,7 +738,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
         // past T) repeat the last page: their keys are masked
         int pg = (ja == j0 && i == tid) ? pg_pre : pt[min(pg_lo + i, n_valid - 1)];
         if (pg < 0 || pg >= p.pool_pages) {
-          pg = 0;
+          pg = -1;
           set_err(p.err, DVS_ERR_BAD_PAGE);
         }
         s_pages[i] = pg;
@@ -751,7 +753,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
 #pragma unroll
         for (int j = 0; j < K_INS; ++j) {
           const int seg = w * K_INS + j;
-          const int pg = __builtin_amdgcn_readfirstlane(s_pages[pbase + seg / SEGPP_K]);
+          const int pg = max(__builtin_amdgcn_readfirstlane(s_pages[pbase + seg / SEGPP_K]), 0);
           const char* base = kpb + ((size_t)pg * p.Hkv + kvh) * PAGE_K;
           __builtin_amdgcn_global_load_lds((const void*)(base + koff[j]),
               (__attribute__((address_space(3))) void*)(stage + seg * 1024), 16, 0, 0);
@@ -759,7 +761,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
 #pragma unroll
         for (int j = 0; j < V_INS; ++j) {
           const int seg = w * V_INS + j;
-          const int pg = __builtin_amdgcn_readfirstlane(s_pages[pbase + seg / SEGPP_V]);
+          const int pg = max(__builtin_amdgcn_readfirstlane(s_pages[pbase + seg / SEGPP_V]), 0);
           const char* base = vpb + ((size_t)pg * p.Hkv + kvh) * PAGE_V;
           __builtin_amdgcn_global_load_lds((const void*)(base + voff[j]),
               (__attribute__((address_space(3))) void*)(stage + KTILE_B + seg * 1024), 16, 0, 0);
@@ -774,12 +776,14 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
         append = false;
         const int n_c = min(n_pre, max(0, L / KT - ja));
         for (; i0 < n_c; ++i0) issue(i0);
-        append_window<D, NT>(tid, wa, wb, L, s, R, p.Hkv, kvh, pt, p.pool_pages, kpb, vpb, knb, vnb);
+        append_window<D, NT>(tid, wa, wb, L, s, R, p.Hkv, kvh,
+                             [&](int i) { return i < pg_hi ? s_pages[i - pg_lo] : pt[i]; }, p.pool_pages,
+                             kpb, vpb, knb, vnb);
         wait_vmcnt<0>();
         __syncthreads();
       }
       for (; i0 < n_pre; ++i0) issue(i0);
-      int left = BAL ? 0 : p.chunk_tiles - (ja - j0) % p.chunk_tiles;   // tiles left in the chunk
+      int left = BAL ? 0 : chunk_tiles - (ja - j0) % chunk_tiles;   // tiles left in the chunk
       for (int i = 0; i < n_main; ++i) {
         wait_tiles<NPL>(min(i == 0 ? NST - 1 : NST - 2, n_main - 1 - i));
         __builtin_amdgcn_s_barrier();     // tile i complete for every wave; tile i-1 consumed
@@ -798,7 +802,7 @@ __global__ void __launch_bounds__(NW * 64, PER_CU) attn_bf16_kernel(AttnParams p
           if (--left == 0 || j + 1 == j1) {
             finish();
             ++k;
-            left = p.chunk_tiles;
+            left = chunk_tiles;
 #pragma unroll
             for (int dg = 0; dg < DG; ++dg) o[dg] = f32x16{};
             m = -INFINITY;
@@ -1182,7 +1186,7 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
         if (wa < wb) {
           int tidw = tidv;   // opaque: nothing of the append is hoisted out of it
           asm volatile("" : "+v"(tidw));
-          append_window<D, NP * 128>(tidw, wa, wb, L, s, R, p.Hkv, kvh, pt, p.pool_pages, kpb, vpb, knb, vnb);
+          append_window<D, NP * 128>(tidw, wa, wb, L, s, R, p.Hkv, kvh, [&](int i) { return pt[i]; }, p.pool_pages, kpb, vpb, knb, vnb);
           wait_vmcnt<0>();
           __syncthreads();
         }
@@ -1731,8 +1735,8 @@ __global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
   const int j = L / KT + (int)blockIdx.x;
   const int a = max(L, j * KT), b = min(T, (j + 1) * KT);
   if (a >= b) return;
-  append_window<D, 256>(threadIdx.x, a, b, L, s, p.R, p.Hkv, kvh, p.page_table + (size_t)s * p.max_pages,
-                        p.pool_pages, (char*)p.k_pool, (char*)p.v_pool, (const char*)p.k_new,
+  const int32_t* __restrict__ pt = p.page_table + (size_t)s * p.max_pages;
+  append_window<D, 256>(threadIdx.x, a, b, L, s, p.R, p.Hkv, kvh, [&](int i) { return pt[i]; }, p.pool_pages, (char*)p.k_pool, (char*)p.v_pool, (const char*)p.k_new,
                         (const char*)p.v_new);
 }
 
@@ -1826,6 +1830,13 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
   return pl;
 }
 
+// Arguments ahead of AttnParams: what a workgroup needs for its first loads.
+// They arrive in registers (kernel-argument preload), where the struct is a
+// load from memory away.
+#define ATTN_HEAD_ARGS(p)                                                                        \
+  (p).kv_len, (p).page_table, (p).q, (p).R, (p).G, (p).Hkv * (p).n_row_tiles, (p).n_row_tiles,   \
+      (p).n_items, (p).xcd_run, (p).max_pages, (p).chunk_tiles, (p).wgs_per_item
+
 template <int D>
 static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
   const dim3 gr(pl.grid);
@@ -1836,9 +1847,9 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
     if (prm.appended)
       hipLaunchKernelGGL(attn_append_kernel<D>, dim3((prm.R + KT - 1) / KT + 1, prm.Hkv, prm.S), dim3(256), 0, st, prm);
     if (pl.per_cu == 2 || NST2 == 4)
-      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, prm);
+      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
     else
-      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, prm);
+      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
     return;
   }
   if (pl.pc) {
@@ -1847,9 +1858,9 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
   }
   // (more than 128 rows take the producer/consumer kernel)
   switch (pl.nw) {
-    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, D == 64 ? 4 : 2, 2>), gr, dim3(256), 0, st, prm); break;
-    case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, prm); break;
-    default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1, true, NSTAGE, 1>), gr, dim3(64), 0, st, prm); break;
+    case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, D == 64 ? 4 : 2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
+    case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
+    default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1, true, NSTAGE, 1>), gr, dim3(64), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
   }
 }
 
