@@ -190,7 +190,7 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, const float* __
 
 template <int WM, int WN, int RG, int CG, int NS, int EPI>
 __global__ void __launch_bounds__(WM * WN * 64, (NS * (WM * RG + WN * CG) * 4096 <= 81920 && WM * WN == 4) ? 2 : 1)
-gemm_tile_kernel(GemmArgs g) {
+gemm_tile_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   constexpr int NW = WM * WN, NT = NW * 64;
   constexpr int MT = WM * RG * 32, CT = WN * CG * 32;    // tile rows, columns
   constexpr int KC = 64, RB = KC * 2;
@@ -205,7 +205,7 @@ gemm_tile_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int nct = (g.ncols + CT - 1) / CT, nrt = g.n_rt;
+  const int nct = (ncols + CT - 1) / CT, nrt = n_rt;
   // order: strips of GM row tiles, column-major inside; each XCD takes a
   // contiguous run of the sequence
   constexpr int GM = MT >= 256 ? 4 : 8;
@@ -220,13 +220,13 @@ gemm_tile_kernel(GemmArgs g) {
 
   auto sw = [](int row) { return (row >> 1) & 7; };
   const int crow = lane >> 3, cchk = lane & 7;
-  const bool rope_call = EPI == EPI_BF16 && g.rope_tab != nullptr;
+  const bool rope_call = EPI == EPI_BF16 && rope_D != 0;
   const __bf16* src[PW];
 #pragma unroll
   for (int i = 0; i < PW; ++i) {
     const int row = (w * PW + i) * 8 + crow;             // row of the stage: A rows, then W rows
     if (w * PW + i < MT / 8) {
-      src[i] = g.A + (size_t)min(m0 + row, g.M - 1) * g.K;
+      src[i] = hA + (size_t)min(m0 + row, M - 1) * K;
     } else {
       const int cw = row - MT;                           // column of the tile
       const int col = c0 + cw;
@@ -234,26 +234,24 @@ gemm_tile_kernel(GemmArgs g) {
       int rowi, n;
       if (EPI == EPI_SWIGLU) {
         rowi = (col >> 5) * 16 + (col & 15);
-        base = (col & 16) ? g.seg[1].W : g.seg[0].W;
-        n = g.seg[0].n;
+        base = (col & 16) ? hW1 : hW0;
+        n = n1;
       } else {
-        int si = 0;
-        if (g.nseg > 1 && col >= g.seg[1].n0) si = 1;
-        if (g.nseg > 2 && col >= g.seg[2].n0) si = 2;
-        rowi = col - g.seg[si].n0;
-        n = g.seg[si].n;
-        base = g.seg[si].W;
-        if (rope_call && si < 2) {
-          const int hd = rowi / g.rope_D, cp = rowi - hd * g.rope_D;
+        const ColSeg cs = col_seg(col, hW0, hW1, hW2, ncols, n1, n2);
+        rowi = col - cs.n0;
+        n = cs.n;
+        base = cs.W;
+        if (rope_call && cs.si < 2) {
+          const int hd = rowi / rope_D, cp = rowi - hd * rope_D;
           const int bh = cp >> 5, c = cp & 31;
-          rowi = hd * g.rope_D + (c < 16 ? bh * 16 + c : g.rope_D / 2 + bh * 16 + c - 16);
+          rowi = hd * rope_D + (c < 16 ? bh * 16 + c : rope_D / 2 + bh * 16 + c - 16);
         }
       }
-      src[i] = base + (size_t)(rowi < n ? rowi : 0) * g.K;
+      src[i] = base + (size_t)(rowi < n ? rowi : 0) * K;
     }
     src[i] += (cchk ^ sw(row)) << 3;
   }
-  const int nch = g.K / KC;
+  const int nch = K / KC;
   const int cps = nch / g.ksplit;                        // chunks per split
   auto issue_one = [&](int t, int slot, int i) {         // copy i of the wave's PW copies of chunk t
     __builtin_amdgcn_global_load_lds((const void*)(src[i] + t * KC),

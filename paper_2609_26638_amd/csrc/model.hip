@@ -517,6 +517,33 @@ struct GemmArgs {
   int ksplit;        // logical K splits (gemm_ksplit)
 };
 
+// Arguments of the GEMM kernels ahead of GemmArgs: what the first copies
+// need.  They arrive in registers (kernel-argument preload); from the struct
+// they were a chain of loads from memory in front of every launch's stream.
+// n1, n2: first column of segments 1 and 2 (past every column if absent); for
+// EPI_SWIGLU n1 is the number of gate (and up) rows; for EPI_F32_ADD (one
+// segment) hW1 is the residual array.
+#define GEMM_HEAD_PARAMS                                                                          \
+  const __bf16 *__restrict__ hA, const __bf16 *__restrict__ hW0, const __bf16 *__restrict__ hW1,  \
+      const __bf16 *__restrict__ hW2, int K, int M, int n_rt, int ncols, int n1, int n2, int rope_D
+#define GEMM_HEAD_ARGS(g)                                                                         \
+  (g).A, (g).seg[0].W, (g).epi == EPI_F32_ADD ? (const __bf16*)(g).seg[0].C : (g).seg[1].W,       \
+      (g).seg[2].W, (g).K, (g).M, (g).n_rt, (g).ncols,             \
+      (g).epi == EPI_SWIGLU ? (g).seg[0].n : (g).nseg > 1 ? (g).seg[1].n0 : 0x7fffffff,           \
+      (g).nseg > 2 ? (g).seg[2].n0 : 0x7fffffff, (g).rope_tab ? (g).rope_D : 0
+
+// Segment of an output column, its weights, first column and columns.
+struct ColSeg {
+  int si, n0, n;
+  const __bf16* W;
+};
+__device__ __forceinline__ ColSeg col_seg(int col, const __bf16* W0, const __bf16* W1, const __bf16* W2,
+                                          int ncols, int n1, int n2) {
+  if (col < n1) return ColSeg{0, 0, min(n1, ncols), W0};
+  if (col < n2) return ColSeg{1, n1, min(n2, ncols) - n1, W1};
+  return ColSeg{2, n2, ncols - n2, W2};
+}
+
 __device__ __forceinline__ uint64_t pack_logit(float v, int idx, bool& nonfinite) {
   uint32_t u = __float_as_uint(v);
   if ((u & 0x7f800000u) == 0x7f800000u) nonfinite = true;
@@ -553,22 +580,21 @@ __device__ __forceinline__ void ring_barrier() {
 // that the epilogue does not wait for them; unit u0 + tid of the epilogue's
 // loop is cpre[u0 / 256].
 template <int MT, int CB, int CW>
-__device__ __forceinline__ void ws_residual_prefetch(const GemmArgs& g, int tid, int m0, int cg, int si,
-                                                     f32x4* cpre) {
+__device__ __forceinline__ void ws_residual_prefetch(const float* __restrict__ C, int M, int n, int tid,
+                                                     int m0, int cg, f32x4* cpre) {
   constexpr int TW = CB * 32;
   constexpr int UNITS = MT * TW / 4;
-  const GemmSeg sg = g.seg[si];
-  const bool vec = (sg.n & 3) == 0;
+  const bool vec = (n & 3) == 0;
 #pragma unroll
   for (int u0 = 0; u0 < UNITS; u0 += 256) {
     const int u = u0 + tid;
     const int r = u / (TW / 4), cc = (u % (TW / 4)) * 4;
     const int c = cc & 31;
     const int row = m0 + r;
-    const int col = (cg * CB + (cc >> 5)) * CW + c - sg.n0;
+    const int col = (cg * CB + (cc >> 5)) * CW + c;
     cpre[u0 / 256] = f32x4{0.f, 0.f, 0.f, 0.f};
-    if (u < UNITS && row < g.M && c < CW && vec && col + 4 <= sg.n)
-      cpre[u0 / 256] = *(const f32x4*)((const float*)sg.C + (size_t)row * sg.n + col);
+    if (u < UNITS && row < M && c < CW && vec && col + 4 <= n)
+      cpre[u0 / 256] = *(const f32x4*)(C + (size_t)row * n + col);
   }
 }
 
@@ -728,7 +754,7 @@ __device__ __forceinline__ void ws_epilogue(const GemmArgs& g, const float* __re
 // (A is re-read once per CB blocks instead of once per block); per element
 // the arithmetic is the single block's.
 template <int MT, int CWT, int CB, int EPI, bool WK, bool FEW = false>
-__global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
+__global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   constexpr int CW = CWT;                  // output columns per block (32, or 16 or 8: narrow)
   constexpr bool NARROW = CWT < 32;
   // k per chunk.  WK (calls of at most one workgroup per CU): 64, so that a
@@ -763,12 +789,12 @@ __global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int NB = (g.ncols + CW - 1) / CW;  // blocks
+  const int NB = (ncols + CW - 1) / CW;  // blocks
   const int NG = (NB + CB - 1) / CB;       // groups of CB blocks
   // XCD-aware order: groups b, b + 8, b + 16, ... share an XCD; the row
   // tiles of one group are consecutive among them
   const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int cg = (j / g.n_rt) * 8 + x, rt = j % g.n_rt;
+  const int cg = (j / n_rt) * 8 + x, rt = j % n_rt;
   if (cg >= NG) return;
   const int m0 = rt * MT;
   char* ring = s_ring + w * NS * CHB;
@@ -782,12 +808,12 @@ __global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
   // checks it).
   const int crow = lane / (RB / 16), cchk = lane % (RB / 16);
   auto sw = [](int row) { return KC == 64 ? (row >> 1) & 7 : (row >> 2) & 3; };
-  int si = 0;
-  if (EPI != EPI_SWIGLU)
-    while (si + 1 < g.nseg && cg * CB * CW >= g.seg[si + 1].n0) ++si;
-  const bool rope = EPI == EPI_BF16 && g.rope_tab != nullptr && si < 2;
+  const ColSeg cs = EPI == EPI_SWIGLU ? ColSeg{0, 0, n1, hW0}
+                                      : col_seg(cg * CB * CW, hW0, hW1, hW2, ncols, n1, n2);
+  const int si = cs.si;
+  const bool rope = EPI == EPI_BF16 && rope_D != 0 && si < 2;
   f32x4 cpre[(MT * CB * 32 / 4 + 255) / 256];
-  if constexpr (EPI == EPI_F32_ADD) ws_residual_prefetch<MT, CB, CW>(g, tid, m0, cg, si, cpre);
+  if constexpr (EPI == EPI_F32_ADD) ws_residual_prefetch<MT, CB, CW>((const float*)hW1, M, ncols, tid, m0, cg, cpre);
   const __bf16* wsrc[CB][WI];  // this lane's weight rows (block b, tile rows 8i + L/8)
 #pragma unroll
   for (int b = 0; b < CB; ++b)
@@ -800,29 +826,29 @@ __global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
       int rowi;
       if (EPI == EPI_SWIGLU) {
         rowi = cb * 16 + (r & 15);
-        valid = rowi < g.seg[0].n;
-        base = r < 16 ? g.seg[0].W : g.seg[1].W;
+        valid = rowi < n1;
+        base = r < 16 ? hW0 : hW1;
       } else {
-        rowi = c0 - g.seg[si].n0 + r;
+        rowi = c0 - cs.n0 + r;
         if (rope) {
           // block bh of a head holds dims bh*P .. bh*P+P-1 and their
           // rotate-half partners D/2 + bh*P ..
-          const int hd = rowi / g.rope_D, cp = rowi - hd * g.rope_D;
+          const int hd = rowi / rope_D, cp = rowi - hd * rope_D;
           const int bh = cp / CW, c = cp - bh * CW;
-          rowi = hd * g.rope_D + (c < CW / 2 ? bh * (CW / 2) + c : g.rope_D / 2 + bh * (CW / 2) + c - CW / 2);
+          rowi = hd * rope_D + (c < CW / 2 ? bh * (CW / 2) + c : rope_D / 2 + bh * (CW / 2) + c - CW / 2);
         }
-        valid = rowi < g.seg[si].n;
-        base = g.seg[si].W;
+        valid = rowi < cs.n;
+        base = cs.W;
       }
-      wsrc[b][i] = base + (size_t)(valid ? rowi : 0) * g.K + ((cchk ^ sw(r)) << 3);
+      wsrc[b][i] = base + (size_t)(valid ? rowi : 0) * K + ((cchk ^ sw(r)) << 3);
     }
   const __bf16* asrc[AI];
 #pragma unroll
   for (int i = 0; i < AI; ++i) {
     const int r = RPI * i + crow;
-    asrc[i] = g.A + (size_t)min(m0 + r, g.M - 1) * g.K + ((cchk ^ sw(r)) << 3);
+    asrc[i] = hA + (size_t)min(m0 + r, M - 1) * K + ((cchk ^ sw(r)) << 3);
   }
-  const int kq = g.K / GK_SPLITS;
+  const int kq = K / GK_SPLITS;
   const int kw = w * kq;               // this wave's split
   const int nch = kq / KC;
   auto issue = [&](int t) {
@@ -900,8 +926,8 @@ __global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
   for (int b = 0; b < CB; ++b) {
     const int cb = cg * CB + b, c0 = cb * CW;
     bool wvalid;
-    if (EPI == EPI_SWIGLU) wvalid = cb * 16 + (l32 & 15) < g.seg[0].n;
-    else wvalid = l32 < CW && c0 - g.seg[si].n0 + l32 < g.seg[si].n;
+    if (EPI == EPI_SWIGLU) wvalid = cb * 16 + (l32 & 15) < n1;
+    else wvalid = l32 < CW && c0 - cs.n0 + l32 < cs.n;
 #pragma unroll
     for (int a = 0; a < RG; ++a)
 #pragma unroll
@@ -931,7 +957,7 @@ __global__ void __launch_bounds__(256, WK ? 1 : 2) gemm_ws_kernel(GemmArgs g) {
 constexpr int NS_BLOCKS = 4;   // 32-column blocks per workgroup
 template <int EPI, int MT, int NS>
 __global__ void __launch_bounds__(256, NS * (MT * 128 + NS_BLOCKS * 4096) <= 81920 ? 2 : 1)
-gemm_ns_kernel(GemmArgs g) {
+gemm_ns_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   constexpr int RG = MT / 32, CW = 32, KC = 64, RB = KC * 2;
   constexpr int AB = MT * RB;                   // A part of a stage: 4 or 8 KB
   constexpr int WB = 32 * RB;                   // one block's weight rows: 4 KB
@@ -944,11 +970,11 @@ gemm_ns_kernel(GemmArgs g) {
   const int tid = threadIdx.x, lane = tid & 63;
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
-  const int NB = (g.ncols + CW - 1) / CW;
+  const int NB = (ncols + CW - 1) / CW;
   const int NG = (NB + NS_BLOCKS - 1) / NS_BLOCKS;
   // XCD-aware order, as in gemm_ws_kernel
   const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int cg = (j / g.n_rt) * 8 + x, rt = j % g.n_rt;
+  const int cg = (j / n_rt) * 8 + x, rt = j % n_rt;
   if (cg >= NG) return;
   const int m0 = rt * MT;
 
@@ -956,35 +982,22 @@ gemm_ns_kernel(GemmArgs g) {
   // takes row 8i + L/8 and 16-byte chunk (L & 7) ^ sw(row)
   const int crow = lane >> 3, cchk = lane & 7;
   auto sw = [](int row) { return (row >> 1) & 7; };
-  int si = 0;
-  if (EPI != EPI_SWIGLU)
-    while (si + 1 < g.nseg && cg * NS_BLOCKS * CW >= g.seg[si + 1].n0) ++si;
+  const int si = 0;                             // (one segment: the LM head)
   const int cb = cg * NS_BLOCKS + w;            // this wave's block
   const __bf16* wsrc[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int r = 8 * i + crow;
-    const __bf16* base;
-    bool valid;
-    int rowi;
-    if (EPI == EPI_SWIGLU) {
-      rowi = cb * 16 + (r & 15);
-      valid = rowi < g.seg[0].n;
-      base = r < 16 ? g.seg[0].W : g.seg[1].W;
-    } else {
-      rowi = cb * CW - g.seg[si].n0 + r;
-      valid = rowi < g.seg[si].n;
-      base = g.seg[si].W;
-    }
-    wsrc[i] = base + (size_t)(valid ? rowi : 0) * g.K + ((cchk ^ sw(r)) << 3);
+    const int rowi = cb * CW + r;
+    wsrc[i] = hW0 + (size_t)(rowi < ncols ? rowi : 0) * K + ((cchk ^ sw(r)) << 3);
   }
   const __bf16* asrc[AI];                       // A rows 8(AI w + i) + L/8
 #pragma unroll
   for (int i = 0; i < AI; ++i) {
     const int r = 8 * (AI * w + i) + crow;
-    asrc[i] = g.A + (size_t)min(m0 + r, g.M - 1) * g.K + ((cchk ^ sw(r)) << 3);
+    asrc[i] = hA + (size_t)min(m0 + r, M - 1) * K + ((cchk ^ sw(r)) << 3);
   }
-  const int nch = g.K / KC;                     // a multiple of 4 (K % 256 == 0)
+  const int nch = K / KC;                     // a multiple of 4 (K % 256 == 0)
   const int cps = nch / GK_SPLITS;              // chunks per split
   auto issue = [&](int t) {
     char* stage = s_ring + (t % NS) * STB;
@@ -1051,9 +1064,7 @@ gemm_ns_kernel(GemmArgs g) {
   // the splits in order, in registers; rows of W past the segment end were
   // read from row 0: their columns are 0.  The summed tile goes to LDS (the
   // ring is free once every wave is done) for the shared epilogue.
-  bool wvalid;
-  if (EPI == EPI_SWIGLU) wvalid = cb * 16 + (l32 & 15) < g.seg[0].n;
-  else wvalid = cb * CW - g.seg[si].n0 + l32 < g.seg[si].n;
+  const bool wvalid = cb * CW + l32 < ncols;
   __syncthreads();
   float* s_sum = (float*)s_ring;
 #pragma unroll
@@ -1078,7 +1089,7 @@ gemm_ns_kernel(GemmArgs g) {
 // meet in LDS and the shared epilogue adds them in order: bit-identical to
 // gemm_ws_kernel.  Serves Q|K|V (rotary epilogue) of calls of more than one
 // workgroup per CU.
-__global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
+__global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   constexpr int MT = 64, CW = 32, KC = 64, RB = KC * 2;
   constexpr int CB = 1, EPI = EPI_BF16;
   constexpr int AB = MT * RB;                   // one K half's A chunk: 8 KB
@@ -1096,46 +1107,39 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
   const int wl = w & 1, kh = w >> 1;            // row group and K half of this wave
-  const int NB = (g.ncols + CW - 1) / CW;
-  const int NG = (NB + CB - 1) / CB;
+  const int NB = (ncols + CW - 1) / CW;
   const int x = blockIdx.x & 7, j = blockIdx.x >> 3;
-  const int cg = (j / g.n_rt) * 8 + x, rt = j % g.n_rt;
-  if (cg >= NG) return;
+  const int cg = (j / n_rt) * 8 + x, rt = j % n_rt;
+  if (cg >= NB) return;
   const int m0 = rt * MT;
   const int crow = lane >> 3, cchk = lane & 7;
   auto sw = [](int row) { return (row >> 1) & 7; };
-  int si = 0;
-  while (si + 1 < g.nseg && cg * CB * CW >= g.seg[si + 1].n0) ++si;
-  const bool rope = EPI == EPI_BF16 && g.rope_tab != nullptr && si < 2;
-  const int cb = cg;
+  const ColSeg cs = col_seg(cg * CW, hW0, hW1, hW2, ncols, n1, n2);
+  const int si = cs.si;
+  const bool rope = rope_D != 0 && si < 2;
   // weight rows this wave copies: rows 16 (w & 1) .. + 15 of the shared block
   const __bf16* wsrc[WIW];
 #pragma unroll
   for (int i = 0; i < WIW; ++i) {
     const int r = 16 * wl + 8 * i + crow;
-    const __bf16* base;
-    bool valid;
-    int rowi;
-    rowi = cb * CW - g.seg[si].n0 + r;
+    int rowi = cg * CW - cs.n0 + r;
     if (rope) {
       // block bh of a head holds dims bh*16 .. bh*16+15 and their
       // rotate-half partners D/2 + bh*16 ..
-      const int hd = rowi / g.rope_D, cp = rowi - hd * g.rope_D;
+      const int hd = rowi / rope_D, cp = rowi - hd * rope_D;
       const int bh = cp / CW, c = cp - bh * CW;
-      rowi = hd * g.rope_D + (c < CW / 2 ? bh * (CW / 2) + c : g.rope_D / 2 + bh * (CW / 2) + c - CW / 2);
+      rowi = hd * rope_D + (c < CW / 2 ? bh * (CW / 2) + c : rope_D / 2 + bh * (CW / 2) + c - CW / 2);
     }
-    valid = rowi < g.seg[si].n;
-    base = g.seg[si].W;
-    wsrc[i] = base + (size_t)(valid ? rowi : 0) * g.K + ((cchk ^ sw(r)) << 3);
+    wsrc[i] = cs.W + (size_t)(rowi < cs.n ? rowi : 0) * K + ((cchk ^ sw(r)) << 3);
   }
   const __bf16* asrc[AI];                       // A rows 32 (w & 1) + 8i + L/8 of half kh
 #pragma unroll
   for (int i = 0; i < AI; ++i) {
     const int r = 32 * wl + 8 * i + crow;
-    asrc[i] = g.A + (size_t)min(m0 + r, g.M - 1) * g.K + ((cchk ^ sw(r)) << 3);
+    asrc[i] = hA + (size_t)min(m0 + r, M - 1) * K + ((cchk ^ sw(r)) << 3);
   }
-  const int kh0 = kh * (g.K / 2);               // first k of this wave's half
-  const int nch = g.K / 2 / KC;                 // chunks per half (even: K % 256 == 0)
+  const int kh0 = kh * (K / 2);               // first k of this wave's half
+  const int nch = K / 2 / KC;                 // chunks per half (even: K % 256 == 0)
   const int cps = nch / 2;                      // chunks per split
   const int wsl0 = 2 * AB + kh * WB;            // stage layout: A of half 0, A of half 1, W of half 0, W of half 1
   auto issue = [&](int t) {
@@ -1194,11 +1198,12 @@ __global__ void __launch_bounds__(256, 2) gemm_nk_kernel(GemmArgs g) {
   // the four split sums to LDS as planes [split][row][TW] (the ring is free
   // once every wave is done); rows of W past the segment end were read from
   // row 0: their columns are 0
-  const bool wvalid = cb * CW - g.seg[si].n0 + l32 < g.seg[si].n;
+  const bool wvalid = cg * CW - cs.n0 + l32 < cs.n;
   __syncthreads();
   float* s_red = (float*)s_ring;
 #pragma unroll
   for (int sp = 0; sp < 2; ++sp)
+#pragma unroll
     for (int i = 0; i < 16; ++i) {
       const int row = 32 * wl + 8 * (i >> 2) + 4 * hh + (i & 3);
       s_red[(2 * kh + sp) * (MT * TW) + row * TW + l32] = wvalid ? acc[sp][i] : 0.f;
@@ -1371,11 +1376,11 @@ static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
   DVS_CHECK_SUPPORTED(total < (1LL << 30), "draft_verify_step: GEMM grid too large");
   const dim3 gr((unsigned)((total + 7) / 8 * 8)), blk(WM * WN * 64);
   switch (g.epi) {
-    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, g); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, g); break;
-    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, g); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, g); break;
-    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, g); break;
+    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
   }
   return launch_status("draft_verify_step(gemm)");
 }
@@ -1402,13 +1407,13 @@ template <int MT, int CWT, int CB, bool WK, bool FEW>
 static void launch_ws_epi(const GemmArgs& g, dim3 gr, hipStream_t st) {
   const dim3 blk(256);
   switch (g.epi) {
-    case EPI_BF16: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_BF16, WK, FEW>), gr, blk, 0, st, g); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32, WK, FEW>), gr, blk, 0, st, g); break;
-    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32_ADD, WK, FEW>), gr, blk, 0, st, g); break;
+    case EPI_BF16: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_BF16, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32_ADD, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
     default:
       if constexpr (CWT == 32) {
-        if (g.epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_SWIGLU, WK, FEW>), gr, blk, 0, st, g);
-        else hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_ARGMAX, WK, FEW>), gr, blk, 0, st, g);
+        if (g.epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_SWIGLU, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
+        else hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_ARGMAX, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
       }
       break;
   }
@@ -1480,8 +1485,8 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
       const long long gridn = (long long)((NGn + 7) / 8) * 8 * g.n_rt;
       DVS_CHECK_SUPPORTED(gridn < (1LL << 31), "draft_verify_step: GEMM grid too large");
       const dim3 grn((unsigned)gridn), blk(256);
-      if (g.epi == EPI_ARGMAX) hipLaunchKernelGGL((gemm_ns_kernel<EPI_ARGMAX, 64, 3>), grn, blk, 0, st, g);
-      else hipLaunchKernelGGL((gemm_ns_kernel<EPI_F32, 64, 3>), grn, blk, 0, st, g);
+      if (g.epi == EPI_ARGMAX) hipLaunchKernelGGL((gemm_ns_kernel<EPI_ARGMAX, 64, 3>), grn, blk, 0, st, GEMM_HEAD_ARGS(g), g);
+      else hipLaunchKernelGGL((gemm_ns_kernel<EPI_F32, 64, 3>), grn, blk, 0, st, GEMM_HEAD_ARGS(g), g);
       return launch_status("draft_verify_step(gemm)");
     }
   }
@@ -1501,13 +1506,13 @@ static int launch_ws(GemmArgs& g, hipStream_t st) {
     g.n_rt = (g.M + TM - 1) / TM;
     const long long total = (long long)g.n_rt * ((g.ncols + TC - 1) / TC);
     hipLaunchKernelGGL((gemm_tile_kernel<4, 2, 1, 1, 4, EPI_SWIGLU>), dim3((unsigned)((total + 7) / 8 * 8)),
-                       dim3(512), 0, st, g);
+                       dim3(512), 0, st, GEMM_HEAD_ARGS(g), g);
     return launch_status("draft_verify_step(gemm)");
   }
   // Q|K|V of more than one workgroup per CU: two row groups times two K
   // halves per workgroup, whole-line chunks, two workgroups per CU
   if (MT == 64 && CB == 1 && !wk && g.epi == EPI_BF16) {
-    hipLaunchKernelGGL((gemm_nk_kernel), gr, dim3(256), 0, st, g);
+    hipLaunchKernelGGL(gemm_nk_kernel, gr, dim3(256), 0, st, GEMM_HEAD_ARGS(g), g);
     return launch_status("draft_verify_step(gemm)");
   }
   if (cw == 8) launch_ws_k<32, 8, 1>(g, gr, wk, st);
