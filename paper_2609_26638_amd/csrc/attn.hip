@@ -767,9 +767,11 @@ attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__
               (__attribute__((address_space(3))) void*)(stage + KTILE_B + seg * 1024), 16, 0, 0);
         }
       };
-      // the whole ring is filled; from then on slot i - 1 is refilled once
-      // every wave is past tile i - 1
-      const int n_pre = min(NST, n_main);
+      // the whole ring is filled (all but one slot where the wait counter
+      // cannot tell the first tile from so many copies); from then on slot
+      // i - 1 is refilled once every wave is past tile i - 1
+      constexpr int PRE = (NST - 1) * NPL < 64 ? NST : NST - 1;
+      const int n_pre = min(PRE, n_main);
       int i0 = 0;
       if (append) {
         // the tiles below L go out first, the append under their copies
@@ -785,9 +787,9 @@ attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__
       for (; i0 < n_pre; ++i0) issue(i0);
       int left = BAL ? 0 : chunk_tiles - (ja - j0) % chunk_tiles;   // tiles left in the chunk
       for (int i = 0; i < n_main; ++i) {
-        wait_tiles<NPL>(min(i == 0 ? NST - 1 : NST - 2, n_main - 1 - i));
+        wait_tiles<NPL>(min(i == 0 ? PRE - 1 : NST - 2, n_main - 1 - i));
         __builtin_amdgcn_s_barrier();     // tile i complete for every wave; tile i-1 consumed
-        if (i > 0 && i + NST - 1 < n_main) issue(i + NST - 1);
+        if ((i > 0 || PRE < NST) && i + NST - 1 < n_main) issue(i + NST - 1);
         const int j = ja + i;
         const bool masked = j >= L / KT;
         bool live = wave_rows;
@@ -1606,20 +1608,28 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
 
 // ---------------------------------------------------------------------------
 // fp32: one workgroup per (sequence, window row, query head); 256 threads.
-// Scores for a 256-key tile in LDS, online softmax over tiles, thread d
-// accumulates output element d.
+// Per 256-key tile: thread j scores key j (its K row in 16-byte loads, all in
+// flight at once; one running fma over the head dim), online softmax over the
+// tiles, and wave w accumulates the output over the tile's pages 4w .. 4w + 3
+// (a head-dim element of a page is 64 contiguous bytes of the pool: four
+// 16-byte loads per element and page); the waves' sums meet at the end.
+// Latency-bound at the sizes it serves (16 rows x 4 heads x 272 keys of 64:
+// 72 -> 14 us; with one element per load and one wave over the 256 keys
+// before).
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
-  __shared__ float sq[D];
-  __shared__ float sp[256];
+  constexpr int DE = (D + 63) / 64;   // head-dim elements per lane: lane, lane + 64
+  __shared__ __attribute__((aligned(16))) float sq[D];
+  __shared__ __attribute__((aligned(16))) float sp[256];
   __shared__ float sred[8];
+  __shared__ float sacc[4][D];
   int idx = blockIdx.x;
   const int h = idx % p.Hq;
   idx /= p.Hq;
   const int r = idx % p.R;
   const int s = idx / p.R;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int kvh = h / p.G;
   const int L = p.kv_len[s];
   const int R = p.R;
@@ -1653,7 +1663,10 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
   if (tid < D) sq[tid] = q[(((size_t)s * R + r) * p.Hq + h) * D + tid];
   __syncthreads();
 
-  float m = -INFINITY, l = 0.f, acc = 0.f;
+  float m = -INFINITY, l = 0.f;
+  float acc[DE];
+#pragma unroll
+  for (int e = 0; e < DE; ++e) acc[e] = 0.f;
   bool bad = false;
   for (int t0 = 0; t0 <= hend; t0 += 256) {
     const int k = t0 + tid;
@@ -1671,48 +1684,105 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
       }
       if (krow) {
         float dot = 0.f;
-        for (int d = 0; d < D; ++d) dot = fmaf(sq[d], krow[d], dot);
+        constexpr int DB = 64;   // elements in flight
+#pragma unroll
+        for (int d0 = 0; d0 < D; d0 += DB) {
+          f32x4 x[DB / 4];
+#pragma unroll
+          for (int d = 0; d < DB / 4; ++d)
+            if (d0 + 4 * d < D) x[d] = *(const f32x4*)(krow + d0 + 4 * d);
+#pragma unroll
+          for (int d = 0; d < DB / 4; ++d)
+            if (d0 + 4 * d < D) {
+              const f32x4 y = *(const f32x4*)(sq + d0 + 4 * d);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) dot = fmaf(y[e], x[d][e], dot);
+            }
+        }
         sc = dot * p.scale;
       }
     }
     // tile max
     float v = sc;
     for (int off = 32; off > 0; off >>= 1) v = fmaxf(v, __shfl_xor(v, off));
-    if ((tid & 63) == 0) sred[tid >> 6] = v;
+    if (lane == 0) sred[w] = v;
     __syncthreads();
     const float tmax = fmaxf(fmaxf(sred[0], sred[1]), fmaxf(sred[2], sred[3]));
-    __syncthreads();
     const float mnew = fmaxf(m, tmax);
     const float alpha = (m == -INFINITY) ? 0.f : expf(m - mnew);
     const float pe = (sc == -INFINITY) ? 0.f : expf(sc - mnew);
     sp[tid] = pe;
     float ps = pe;
     for (int off = 32; off > 0; off >>= 1) ps += __shfl_xor(ps, off);
-    if ((tid & 63) == 0) sred[4 + (tid >> 6)] = ps;
+    if (lane == 0) sred[4 + w] = ps;
     __syncthreads();
     l = l * alpha + ((sred[4] + sred[5]) + (sred[6] + sred[7]));
     m = mnew;
-    if (tid < D) {
-      float a = acc * alpha;
-      const int nk = min(256, hend + 1 - t0);
-      for (int j = 0; j < nk; ++j) {
-        const int kk = t0 + j;
-        float vv;
-        if (kk < L) {
-          const int pg = pt[kk >> 4];
-          if (pg < 0 || pg >= p.pool_pages) continue;
-          vv = vp[(((size_t)pg * p.Hkv + kvh) * D + tid) * 16 + (kk & 15)];
-        } else {
-          vv = vn[(((size_t)s * R + (kk - L)) * p.Hkv + kvh) * D + tid];
+#pragma unroll
+    for (int e = 0; e < DE; ++e) acc[e] *= alpha;
+    // this wave's four pages of the tile, keys in order
+    int pgs[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k0 = t0 + (4 * w + i) * 16;
+      pgs[i] = k0 <= hend && k0 < L ? pt[k0 >> 4] : -1;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int k0 = t0 + (4 * w + i) * 16;
+      const float* pj = sp + (4 * w + i) * 16;
+      if (k0 > hend) break;
+      const bool in_pool = pgs[i] >= 0 && pgs[i] < p.pool_pages;
+      const float* vrow = vp + ((size_t)(in_pool ? pgs[i] : 0) * p.Hkv + kvh) * D * 16;
+      if (k0 + 16 <= L && k0 + 15 <= hend) {
+        if (!in_pool) continue;
+#pragma unroll
+        for (int e = 0; e < DE; ++e) {
+          const int d = lane + 64 * e;
+          if (d < D) {
+            f32x4 x[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) x[c] = *(const f32x4*)(vrow + (size_t)d * 16 + 4 * c);
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+              const f32x4 y = *(const f32x4*)(pj + 4 * c);
+#pragma unroll
+              for (int j = 0; j < 4; ++j) acc[e] = fmaf(y[j], x[c][j], acc[e]);
+            }
+          }
         }
-        a = fmaf(sp[j], vv, a);
+      } else {
+        // the page holds window keys (from v_new: the pool slots may not be
+        // written yet) or ends past the last visible key
+#pragma unroll
+        for (int e = 0; e < DE; ++e) {
+          const int d = lane + 64 * e;
+          if (d < D) {
+            float x[16];
+#pragma unroll
+            for (int j = 0; j < 16; ++j) {
+              const int kk = k0 + j;
+              x[j] = 0.f;
+              if (kk > hend) continue;
+              if (kk >= L) x[j] = vn[(((size_t)s * R + (kk - L)) * p.Hkv + kvh) * D + d];
+              else if (in_pool) x[j] = vrow[(size_t)d * 16 + j];
+            }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) acc[e] = fmaf(pj[j], x[j], acc[e]);
+          }
+        }
       }
-      acc = a;
     }
     __syncthreads();
   }
   if (bad) set_err(p.err, DVS_ERR_BAD_PAGE);
-  if (tid < D) ((float*)p.out)[(((size_t)s * R + r) * p.Hq + h) * D + tid] = acc / l;
+#pragma unroll
+  for (int e = 0; e < DE; ++e)
+    if (lane + 64 * e < D) sacc[w][lane + 64 * e] = acc[e];
+  __syncthreads();
+  if (tid < D)
+    ((float*)p.out)[(((size_t)s * R + r) * p.Hq + h) * D + tid] =
+        ((sacc[0][tid] + sacc[1][tid]) + (sacc[2][tid] + sacc[3][tid])) / l;
 }
 
 // ---------------------------------------------------------------------------

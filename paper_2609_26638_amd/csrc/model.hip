@@ -375,8 +375,7 @@ __global__ void silu_mul_kernel(const T* __restrict__ gate, const T* __restrict_
 
 // ---------------------------------------------------------------------------
 // Generic GEMM: C[m, n] (=, or += into an fp32 residual) sum_k A[m, k] W[n, k]
-// for the fp32 model and for bf16 shapes whose K is not a multiple of 64
-// (small test models).  One wave per 32 output columns; it walks k in
+// for bf16 shapes whose K is not a multiple of 64 (small test models).  One wave per 32 output columns; it walks k in
 // ascending order, loading each weight fragment once and applying it to every
 // 32-row group of A (up to MG_MAX groups, the rest in further passes), so a
 // row's result does not depend on the row count here either.
@@ -1253,49 +1252,69 @@ __global__ void __launch_bounds__(256) argmax_rows_kernel(const uint64_t* __rest
 namespace dvs {
 
 // fp32: v_mfma_f32_32x32x2_f32; lane (row|col, hh) takes k = k0 + 4*hh + j in
-// MFMA j, so one 16-byte load per operand feeds 4 MFMAs.
-__global__ void __launch_bounds__(256) gemm_f32_kernel(const float* __restrict__ A,
-                                                       const float* __restrict__ W, int M, int N,
-                                                       int K, float* __restrict__ Cf, int accumulate) {
-  const int lane = threadIdx.x & 63;
-  const int wave = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  const int n0 = wave * 32;
-  if (n0 >= N) return;
-  const int l32 = lane & 31, hh = lane >> 5;
+// MFMA j, so one 16-byte load per operand feeds 4 MFMAs.  One wave per 32 rows
+// x 32 columns walks k in ascending order (a row's result does not depend on
+// the row count).  Bound by the latency of its loads at the sizes it serves:
+// the fragments of 64 k are read at once, the next 64 under their products
+// (16 rows x 256 columns, K = 256: 22.6 -> 7 us with one step of 8 k in
+// flight before), and each wave is a workgroup, on a CU of its own while there
+// are any.  Up to three weight matrices side by side (Wq|Wk|Wv, gate|up), each
+// of its own column count and output.
+struct F32Segs {
+  const float* W[3];
+  float* C[3];
+  int n[3], nb[3];   // columns; 32-column blocks up to and including this segment
+};
+constexpr int F32_STEPS = 8;   // steps of 8 k read at once
+__global__ void __launch_bounds__(64) gemm_f32_kernel(const float* __restrict__ A, int M, int K,
+                                                      int accumulate, F32Segs sg) {
+  const int lane = threadIdx.x, l32 = lane & 31, hh = lane >> 5;
+  const int blk = blockIdx.x;
+  const int si = blk < sg.nb[0] ? 0 : (blk < sg.nb[1] ? 1 : 2);
+  const float* __restrict__ W = si == 0 ? sg.W[0] : (si == 1 ? sg.W[1] : sg.W[2]);
+  float* __restrict__ Cf = si == 0 ? sg.C[0] : (si == 1 ? sg.C[1] : sg.C[2]);
+  const int N = si == 0 ? sg.n[0] : (si == 1 ? sg.n[1] : sg.n[2]);
+  const int n0 = (blk - (si == 0 ? 0 : sg.nb[si - 1])) * 32, m0 = blockIdx.y * 32;
   const int ncol = n0 + l32;
-  const bool nvalid = ncol < N;
-  const float* wrow = W + (size_t)(nvalid ? ncol : n0) * K;
-  for (int m0 = 0; m0 < M; m0 += MG_MAX * 32) {
-    const int ng = min(MG_MAX, (M - m0 + 31) / 32);
-    f32x16 acc[MG_MAX];
+  const bool nvalid = ncol < N, mvalid = m0 + l32 < M;
+  // rows and columns past the end read the first one's and are not written
+  const float* wrow = W + (size_t)(nvalid ? ncol : n0) * K + hh * 4;
+  const float* arow = A + (size_t)(mvalid ? m0 + l32 : m0) * K + hh * 4;
+  f32x16 acc = f32x16{};
+  f32x4 fa[2][F32_STEPS], fb[2][F32_STEPS];
+  auto load = [&](int k0, f32x4 (&xa)[F32_STEPS], f32x4 (&xb)[F32_STEPS]) {
 #pragma unroll
-    for (int g = 0; g < MG_MAX; ++g) acc[g] = f32x16{};
-    for (int k0 = 0; k0 < K; k0 += 8) {
-      const f32x4 b = nvalid ? *(const f32x4*)(wrow + k0 + hh * 4) : f32x4{};
-#pragma unroll
-      for (int g = 0; g < MG_MAX; ++g) {
-        if (g < ng) {
-          const int mrow = m0 + g * 32 + l32;
-          const f32x4 a = mrow < M ? *(const f32x4*)(A + (size_t)mrow * K + k0 + hh * 4) : f32x4{};
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-            acc[g] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc[g], 0, 0, 0);
-        }
-      }
+    for (int u = 0; u < F32_STEPS; ++u) {
+      const int k = min(k0 + 8 * u, K - 8);   // (past the end: read again, not used)
+      xa[u] = *(const f32x4*)(arow + k);
+      xb[u] = *(const f32x4*)(wrow + k);
     }
-    if (!nvalid) continue;
+  };
+  auto mul = [&](int k0, const f32x4 (&xa)[F32_STEPS], const f32x4 (&xb)[F32_STEPS]) {
 #pragma unroll
-    for (int g = 0; g < MG_MAX; ++g) {
-      if (g >= ng) break;
+    for (int u = 0; u < F32_STEPS; ++u)
+      if (k0 + 8 * u < K)
 #pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int mrow = m0 + g * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
-        if (mrow >= M) continue;
-        const size_t o = (size_t)mrow * N + ncol;
-        if (accumulate) Cf[o] += acc[g][i];
-        else Cf[o] = acc[g][i];
-      }
+        for (int j = 0; j < 4; ++j) acc = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[u][j], xb[u][j], acc, 0, 0, 0);
+  };
+  constexpr int KB = 8 * F32_STEPS;
+  load(0, fa[0], fb[0]);
+  for (int k0 = 0; k0 < K; k0 += 2 * KB) {
+    if (k0 + KB < K) load(k0 + KB, fa[1], fb[1]);
+    mul(k0, fa[0], fb[0]);
+    if (k0 + KB < K) {
+      if (k0 + 2 * KB < K) load(k0 + 2 * KB, fa[0], fb[0]);
+      mul(k0 + KB, fa[1], fb[1]);
     }
+  }
+  if (!nvalid) return;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    const int mrow = m0 + 8 * (i >> 2) + 4 * hh + (i & 3);
+    if (mrow >= M) continue;
+    const size_t o = (size_t)mrow * N + ncol;
+    if (accumulate) Cf[o] += acc[i];
+    else Cf[o] = acc[i];
   }
 }
 
@@ -1532,6 +1551,20 @@ static int launch_gemm(GemmArgs& g, hipStream_t st) {
   return use_ws(g.M, g.K) ? launch_ws(g, st) : launch_tile(g, st);
 }
 
+// fp32 products of one A with nseg weight matrices side by side.
+static int gemm_f32(const void* A, F32Segs sg, int nseg, int M, int K, int accumulate, hipStream_t st) {
+  int nb = 0;
+  for (int i = 0; i < 3; ++i) {
+    if (i < nseg) nb += (sg.n[i] + 31) / 32;
+    sg.nb[i] = nb;
+  }
+  const long long nm = ((long long)M + 31) / 32;
+  DVS_CHECK_SUPPORTED(nm <= 65535, "draft_verify_step: fp32 GEMM of %d rows", M);
+  hipLaunchKernelGGL(gemm_f32_kernel, dim3(nb, (unsigned)nm), dim3(64), 0, st, (const float*)A, M, K,
+                     accumulate, sg);
+  return launch_status("draft_verify_step(gemm)");
+}
+
 // C = A W^T (or C += for the fp32 residual).  `c_f32` selects an fp32 output
 // for bf16 models (residual stream, logits); fp32 models always write fp32.
 static int gemm(int dtype, const void* A, const void* W, int M, int N, int K, void* C, int c_f32,
@@ -1544,13 +1577,14 @@ static int gemm(int dtype, const void* A, const void* W, int M, int N, int K, vo
     g.epi = c_f32 ? (accumulate ? EPI_F32_ADD : EPI_F32) : EPI_BF16;
     return launch_gemm(g, st);
   }
+  if (dtype == DVS_F32) {
+    F32Segs sg{};
+    sg.W[0] = (const float*)W; sg.C[0] = (float*)C; sg.n[0] = N;
+    return gemm_f32(A, sg, 1, M, K, accumulate, st);
+  }
   const int blocks = ((N + 31) / 32 + 3) / 4;
-  if (dtype == DVS_BF16)
-    hipLaunchKernelGGL(gemm_bf16_kernel, dim3(blocks), dim3(256), 0, st, (const __bf16*)A,
-                       (const __bf16*)W, M, N, K, C, c_f32, accumulate);
-  else
-    hipLaunchKernelGGL(gemm_f32_kernel, dim3(blocks), dim3(256), 0, st, (const float*)A,
-                       (const float*)W, M, N, K, (float*)C, accumulate);
+  hipLaunchKernelGGL(gemm_bf16_kernel, dim3(blocks), dim3(256), 0, st, (const __bf16*)A,
+                     (const __bf16*)W, M, N, K, C, c_f32, accumulate);
   return launch_status("draft_verify_step(gemm)");
 }
 
@@ -1632,6 +1666,12 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
         g.rope_D = D;
       }
       if ((rc = launch_gemm(g, stream))) return rc;
+    } else if (dt == DVS_F32) {
+      F32Segs sg{{(const float*)ly.wq, (const float*)ly.wk, (const float*)ly.wv},
+                 {(float*)q, (float*)k, (float*)v},
+                 {Hq * D, Hkv * D, Hkv * D},
+                 {}};
+      if ((rc = gemm_f32(h, sg, 3, M, H, 0, stream))) return rc;
     } else {
       if ((rc = gemm(dt, h, ly.wq, M, Hq * D, H, q, 0, 0, stream))) return rc;
       if ((rc = gemm(dt, h, ly.wk, M, Hkv * D, H, k, 0, 0, stream))) return rc;
@@ -1663,8 +1703,16 @@ static int forward_layers(const dvs_model* m, const dvs_state* st, int n_causal,
         g.epi = EPI_SWIGLU;
         if ((rc = launch_gemm(g, stream))) return rc;
       } else {
-        if ((rc = gemm(dt, h, ly.w_gate, M, m->ffn, H, gate, 0, 0, stream))) return rc;
-        if ((rc = gemm(dt, h, ly.w_up, M, m->ffn, H, up, 0, 0, stream))) return rc;
+        if (dt == DVS_F32) {
+          F32Segs sg{{(const float*)ly.w_gate, (const float*)ly.w_up, nullptr},
+                     {(float*)gate, (float*)up, nullptr},
+                     {m->ffn, m->ffn, 0},
+                     {}};
+          if ((rc = gemm_f32(h, sg, 2, M, H, 0, stream))) return rc;
+        } else {
+          if ((rc = gemm(dt, h, ly.w_gate, M, m->ffn, H, gate, 0, 0, stream))) return rc;
+          if ((rc = gemm(dt, h, ly.w_up, M, m->ffn, H, up, 0, 0, stream))) return rc;
+        }
         const long long n = (long long)M * m->ffn;
         hipLaunchKernelGGL(silu_mul_kernel<T>, dim3((unsigned)((n + 255) / 256)), dim3(256), 0,
                            stream, gate, up, n, act);
