@@ -47,7 +47,8 @@
 //     whatever the length mix; only shares that split an item publish
 //     partials.
 //   A split item's partials ((m, l) in fp32; O/l in bf16) are merged in
-//   segment order by the last workgroup to count in; the count-in is an
+//   segment order, by a launch of its own (attn_merge_kernel) or by the last
+//   workgroup to count in; the count-in is an
 //   agent-scope release atomic add on the item's counter, and the workgroup
 //   that counts in last takes an agent-scope acquire fence: the count-ins
 //   form one release sequence, so every workgroup's partial stores are
@@ -68,6 +69,11 @@ constexpr int NSTAGE = 4;              // LDS ring depth of the balanced split
 constexpr int SUB_TILES = 256;         // tiles whose page ids are staged at once
 constexpr int MAX_CHUNK_KEYS = 16384;
 constexpr int BAL_MAX_SEGS = 16;       // balanced mode: segments per item (bound)
+// Merge launches (attn_merge_kernel): output elements of an item, or segments
+// per item, from which on they pay; and the segments its page table must hold.
+constexpr int MERGE_MIN_ELEMS = 4096;
+constexpr int MERGE_MANY_SEGS = 8;
+constexpr int MERGE_MIN_SEGS = 4;
 constexpr int BAL_MAX_SEQS = 1024;     // balanced mode: sequences per call
 constexpr float RESCALE_LOG2 = 8.f;
 
@@ -101,6 +107,8 @@ struct AttnParams {
   int chunk_tiles;   // aligned: tiles per chunk
   int wgs_per_item;  // aligned: workgroups an item's chunks are shared over
   int xcd_run;       // aligned: items of a contiguous run per XCD (0: dealt out in turn)
+  int merge_launch;  // split items are merged by attn_merge_kernel
+  int32_t* meta;     // balanced with merge_launch: segments and first workgroup of an item
   int appended;      // the window's K/V are in the pool already
   int share_min;     // balanced: minimum tiles per workgroup
   int max_segs;      // partial slots per item
@@ -503,6 +511,7 @@ attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__
       k = (int)blockIdx.x - P0 / share;
       nseg = (P0 + tiles - 1) / share - P0 / share + 1;
       nwg = nseg;
+      if (p.merge_launch && k == 0 && tid == 0) p.meta[it] = (nseg << 16) | (int)blockIdx.x;
       u += j1 - j0;
     } else {
       if (!first_segment) break;
@@ -815,6 +824,9 @@ attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__
     }
     if constexpr (BAL) finish();
     if (nseg == 1) continue;
+    // Split items: a launch of its own merges (attn_merge_kernel) ...
+    if (nwg > 1 && p.merge_launch) continue;
+    // ... or the last workgroup here.
     // A workgroup that holds the whole item merges its own partials: every
     // thread reads back what it wrote.  Otherwise wait for the stores, then
     // count in; the workgroup that completes the item merges.
@@ -1793,6 +1805,98 @@ __global__ void attn_zero_kernel(int32_t* __restrict__ p, int n) {
   if (i < n) p[i] = 0;
 }
 
+// Merges the partials of the split items of an attn_bf16_kernel launch, in its
+// layout and segment order (and so with the bits of its own merge): one
+// workgroup per item and 16-byte word of the partials, thread = thread of the
+// attention workgroup, eight segments' words in flight.
+//
+// In the attention kernel the last workgroup of an item merges, after a
+// count-in by each whose release writes back the XCD's L2: at 32 sequences x
+// 128 rows (512 workgroups) that phase was 25 us of an 81 us launch, at 8
+// sequences 7 of 25, at one sequence 12 of 25.  Here the launch boundary
+// orders the partials once, and every CU takes part.
+template <int D, bool BAL>
+__global__ void attn_merge_kernel(const int32_t* __restrict__ kv_len, int R, int G, int HN, int n_row_tiles,
+                                  int max_pages, int chunk_tiles, int wgs_per_item, int max_segs, AttnParams p) {
+  constexpr int NWD = D / 16;
+  const int it = blockIdx.x, jw = blockIdx.y, tid = threadIdx.x, NT = blockDim.x;
+  const int lane = tid & 63, w = tid >> 6, hh = lane >> 5, l32 = lane & 31;
+  const int s = it / HN, qi = it - s * HN;
+  const int kvh = qi / n_row_tiles, rt = qi - kvh * n_row_tiles;
+  const int L = kv_len[s];
+  if (L < 0 || L + R > max_pages * 16) return;
+  const int n = rt * (NT / 2) + w * 32 + l32;
+  int nseg, wg0 = 0;
+  if constexpr (BAL) {
+    const int mt = p.meta[it];
+    nseg = mt >> 16;
+    wg0 = mt & 0xffff;
+    if (nseg <= 1) return;
+  } else {
+    const int rl = (min((rt + 1) * (NT / 2), R * G) - 1) / G;
+    const int seen = max(row_hi(p, L, rl), group_interval(p, L, rl).hi2) + 1;
+    nseg = ((seen + KT - 1) / KT + chunk_tiles - 1) / chunk_tiles;
+    const int run = (nseg + wgs_per_item - 1) / wgs_per_item;
+    if (nseg <= run) return;   // one workgroup held the item
+  }
+  if (n >= R * G) return;
+  auto slot = [&](int c) { return part_slot(BAL, it, max_segs, wg0, c); };
+  auto ml_of = [&](int c) { return *(const f32x2*)(p.part_ml + slot(c) * (NT * 2) + (size_t)tid * 2); };
+  constexpr int SB = 8;
+  float M = -INFINITY;
+  if (nseg > SB) {
+    for (int c0 = 0; c0 < nseg; c0 += 16) {
+      f32x2 mv[16];
+#pragma unroll
+      for (int j = 0; j < 16; ++j) mv[j] = ml_of(min(c0 + j, nseg - 1));
+#pragma unroll
+      for (int j = 0; j < 16; ++j) M = fmaxf(M, mv[j][0]);   // repeats of the last segment are harmless
+    }
+  }
+  float acc[8], lt = 0.f;
+#pragma unroll
+  for (int e = 0; e < 8; ++e) acc[e] = 0.f;
+  for (int c0 = 0; c0 < nseg; c0 += SB) {
+    u32x4 pv[SB];
+    f32x2 mlc[SB];
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+      const int c = min(c0 + b, nseg - 1);
+      pv[b] = *(const u32x4*)((const uint32_t*)p.part_o + slot(c) * (size_t)(NT * NWD * 4) +
+                              (size_t)jw * (NT * 4) + (size_t)tid * 4);
+      mlc[b] = ml_of(c);
+    }
+    if (nseg <= SB) {
+#pragma unroll
+      for (int b = 0; b < SB; ++b) M = fmaxf(M, mlc[b][0]);
+    }
+    const float Ms = (M == -INFINITY) ? 0.f : M;
+#pragma unroll
+    for (int b = 0; b < SB; ++b) {
+      if (c0 + b >= nseg) break;
+      const float wgt = __builtin_amdgcn_exp2f(mlc[b][0] - Ms) * mlc[b][1];
+      lt += wgt;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        acc[2 * e] += wgt * __uint_as_float(pv[b][e] << 16);
+        acc[2 * e + 1] += wgt * __uint_as_float(pv[b][e] & 0xffff0000u);
+      }
+    }
+  }
+  const float inv = lt > 0.f ? 1.f / lt : 0.f;
+  const int r = n / G, h = kvh * G + (n - r * G);
+  // word jw: elements 8 jw .. of the thread's, that is rows of four dims
+  const int d = (jw >> 1) * 32 + 16 * (jw & 1) + 4 * hh;
+  __bf16* orow = (__bf16*)p.out + (((size_t)s * R + r) * p.Hq + h) * D + d;
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const f32x2 v01 = f32x2{acc[4 * g] * inv, acc[4 * g + 1] * inv};
+    const f32x2 v23 = f32x2{acc[4 * g + 2] * inv, acc[4 * g + 3] * inv};
+    *(u32x2*)(orow + 8 * g) = u32x2{__builtin_bit_cast(uint32_t, __builtin_convertvector(v01, bf16x2)),
+                                    __builtin_bit_cast(uint32_t, __builtin_convertvector(v23, bf16x2))};
+  }
+}
+
 // Appends the window's K/V ([L, T)) to the pool, one workgroup per (64-key
 // tile, KV head, sequence): aligned calls of several row tiles, whose
 // workgroups would otherwise each append the whole window again (8832 rows,
@@ -1812,8 +1916,8 @@ __global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
 
 struct AttnPlan {
   int nw, rows_total, rows_per_wg, n_row_tiles, n_items, balanced, pc;
-  int chunk_tiles, n_chunks_max, wgs_per_item, xcd_run, per_cu, share_min, max_segs, grid;
-  size_t off_counters, off_ml, off_o, bytes;
+  int chunk_tiles, n_chunks_max, wgs_per_item, xcd_run, merge_launch, per_cu, share_min, max_segs, grid;
+  size_t off_counters, off_meta, off_ml, off_o, bytes;
 };
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -1873,7 +1977,10 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     // fused step: 1.14 / 1.09 / 1.15 / 1.15 ms with 1 / 2 / 3 / 4 per CU).
     const int want = 2 * device_cus();
     pl.wgs_per_item = std::min(pl.n_chunks_max, (want + pl.n_items - 1) / pl.n_items);
-    pl.per_cu = (long long)pl.wgs_per_item * pl.n_items > device_cus() ? 2 : 1;
+    // Two workgroups per CU also where one would do, except for the 128-wide
+    // heads, whose 256 registers per thread then spill a few (steps of one
+    // sequence, D = 96: 155 -> 148 and 181 -> 172 us; D = 128: 140.7 -> 142.6).
+    pl.per_cu = D != 128 || (long long)pl.wgs_per_item * pl.n_items > device_cus() ? 2 : 1;
     pl.xcd_run = pl.n_row_tiles > 1 && pl.n_items >= 64 ? (pl.n_items + 7) / 8 : 0;
     pl.grid = pl.wgs_per_item * (pl.xcd_run ? 8 * pl.xcd_run : pl.n_items);
   }
@@ -1888,10 +1995,24 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     const size_t ml_b = pl.pc ? (size_t)2 * 256 * sizeof(float) : (size_t)NT * 2 * sizeof(float);
     const size_t o_b = pl.pc ? (size_t)256 * (2 * (D / 32) * 16) * 2
                              : (size_t)NT * (D / 32) * 16 * 2;
+    // A launch of its own merges where the partials are many (more than 4096
+    // output elements per item) or an item is split over many workgroups (8),
+    // and the page table can hold a split worth it (the lengths are not known
+    // here).  In-kernel count-in and merge against the launch, us: 32 x 128
+    // rows of 128 dims 111.4 / 90.2; 1 x 128 rows 25.3 / 19.0; 20 x 68 rows of
+    // 64 dims 23.7 / 21.5; 4 items of 28 rows in 16 segments 28.9 / 25.6; an
+    // AR step of 9 segments 823 / 814; but 28 items of 3 rows in 6 segments
+    // 13.1 / 16.3, 204 items of 8 rows in one or two 44.3 / 46.2.
+    const int segs_max = pl.balanced ? std::min(BAL_MAX_SEGS, max_tiles) : pl.n_chunks_max;
+    const int segs = std::min(segs_max, pl.grid / std::max(1, pl.n_items));
+    pl.merge_launch = !pl.pc && segs_max >= MERGE_MIN_SEGS && (pl.balanced || pl.wgs_per_item > 1) &&
+                      (pl.rows_total * D > MERGE_MIN_ELEMS || segs >= MERGE_MANY_SEGS);
     pl.off_counters = 0;
     // (no counters where one workgroup holds every chunk of its item)
     const bool counted = pl.balanced || pl.wgs_per_item > 1;
-    pl.off_ml = counted ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0;
+    pl.off_meta = counted ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0;
+    pl.off_ml = pl.off_meta +
+                (pl.merge_launch && pl.balanced ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0);
     pl.off_o = pl.off_ml + align256(slots * ml_b);
     pl.bytes = pl.off_o + align256(slots * o_b);
   } else {
@@ -1907,6 +2028,10 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
   (p).kv_len, (p).page_table, (p).q, (p).R, (p).G, (p).Hkv * (p).n_row_tiles, (p).n_row_tiles,   \
       (p).n_items, (p).xcd_run, (p).max_pages, (p).chunk_tiles, (p).wgs_per_item
 
+#define ATTN_MERGE_ARGS(p)                                                                       \
+  (p).kv_len, (p).R, (p).G, (p).Hkv * (p).n_row_tiles, (p).n_row_tiles, (p).max_pages,           \
+      (p).chunk_tiles, (p).wgs_per_item, (p).max_segs
+
 template <int D>
 static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
   const dim3 gr(pl.grid);
@@ -1916,10 +2041,14 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
     prm.appended = pl.n_row_tiles > 1;
     if (prm.appended)
       hipLaunchKernelGGL(attn_append_kernel<D>, dim3((prm.R + KT - 1) / KT + 1, prm.Hkv, prm.S), dim3(256), 0, st, prm);
-    if (pl.per_cu == 2 || NST2 == 4)
+    if constexpr (D == 128) {
+      if (pl.per_cu == 2) hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
+      else hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
+    } else {
       hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
-    else
-      hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
+    }
+    if (pl.merge_launch)
+      hipLaunchKernelGGL((attn_merge_kernel<D, false>), dim3(pl.n_items, D / 16), dim3(256), 0, st, ATTN_MERGE_ARGS(prm), prm);
     return;
   }
   if (pl.pc) {
@@ -1932,13 +2061,15 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
     case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
     default: hipLaunchKernelGGL((attn_bf16_kernel<D, 1, true, NSTAGE, 1>), gr, dim3(64), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
   }
+  if (pl.merge_launch)
+    hipLaunchKernelGGL((attn_merge_kernel<D, true>), dim3(pl.n_items, D / 16), dim3(pl.nw * 64), 0, st, ATTN_MERGE_ARGS(prm), prm);
 }
 
 size_t attn_counter_bytes(int S, int R, int Hq, int Hkv, int D, int max_pages, int chunk_keys,
                           int dtype) {
   if (dtype != DVS_BF16) return 0;
   const AttnPlan pl = plan_attn(S, R, Hq, Hkv, D, max_pages, chunk_keys, dtype);
-  return pl.off_ml - pl.off_counters;
+  return pl.off_meta - pl.off_counters;
 }
 
 }  // namespace dvs
@@ -2010,12 +2141,14 @@ static int attn_launch(const void* q, const void* k_new, const void* v_new, void
   if (dtype == DVS_BF16) {
     char* ws = (char*)workspace;
     prm.counters = (int32_t*)(ws + pl.off_counters);
+    prm.meta = (int32_t*)(ws + pl.off_meta);
+    prm.merge_launch = pl.merge_launch;
     prm.part_ml = (float*)(ws + pl.off_ml);
     prm.part_o = (float*)(ws + pl.off_o);
     DVS_CHECK_SUPPORTED((long long)pl.grid < (1LL << 31), "attn_hybrid_block: grid too large");
     if (scratch_cap > 0) {
       // the array keeps the previous call's contents: clear the counters
-      const int nw = (int)((pl.off_ml - pl.off_counters) / sizeof(int32_t));
+      const int nw = (int)((pl.off_meta - pl.off_counters) / sizeof(int32_t));
       if (nw) hipLaunchKernelGGL(attn_zero_kernel, dim3((nw + 255) / 256), dim3(256), 0, st, prm.counters, nw);
     }
     if (D == 128) launch_bf16<128>(pl, prm, st);

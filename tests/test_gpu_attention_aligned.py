@@ -57,3 +57,31 @@ def test_aligned_chunks(lens, nc, nm, group, Hq, Hkv, D, chunk):
         held = ai.state.page_table[s][:(lens[s] + nc + nm + 15) // 16]
         np.testing.assert_array_equal(to_f64(kp)[held], k_ref[held])
         np.testing.assert_array_equal(to_f64(vp)[held], v_ref[held])
+
+
+# The merge by a launch of its own (many output elements, or many segments)
+# and by the last workgroup, in both splits, at every wave count of the
+# balanced one; one item whole and one split in the same call.
+@pytest.mark.parametrize("lens,R,Hq,Hkv,D,chunk", [
+    ([1500, 30], 8, 16, 4, 128, 0),      # 32 rows, one wave, 16 segments
+    ([1500, 30, 700], 16, 8, 2, 96, 0),  # 64 rows, two waves
+    ([4000, 0], 30, 16, 4, 64, 0),       # 120 rows, four waves
+    ([900, 63], 25, 16, 4, 128, 64),     # 100 rows, aligned
+    ([2000, 5], 1, 8, 2, 64, 64),        # 4 rows in 32 chunks
+    ([300] * 24, 3, 8, 4, 64, 64),       # 6 rows, count-in
+])
+def test_merge(lens, R, Hq, Hkv, D, chunk):
+    ai = synth.make_attn_inputs(9, len(lens), lens, R, 0, Hq, Hkv, D, "bf16", std=1.0, scatter=True)
+    d = dev_attn(ai)
+    ws = dvs.Workspace(256)
+    outs = []
+    for _ in range(3):   # the same workspace: whatever a call leaves in it
+        outs.append(dvs.attn_hybrid_block(d["q"], d["k_new"], d["v_new"], d["k_pool"], d["v_pool"],
+                                          d["page_table"], d["kv_len"], R, 0, ai.scale,
+                                          workspace=ws, chunk_keys=chunk))
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    n = min(len(lens), 3)
+    ref = oa.attn_hybrid_block(ai.as_f64("q")[:n], ai.as_f64("k_new")[:n], ai.as_f64("v_new")[:n],
+                               ai.as_f64("k_pool"), ai.as_f64("v_pool"), ai.state.page_table[:n],
+                               ai.state.kv_len[:n], R, 0, ai.scale)
+    assert max_rel_err(to_f64(outs[0][:n]), ref) <= 2e-2
