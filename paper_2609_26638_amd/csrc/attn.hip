@@ -1960,12 +1960,10 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     }
     if (pl.share_min < 1) pl.share_min = 1;
     pl.max_segs = BAL_MAX_SEGS;
-    // 97 .. 128 rows (four waves): two workgroups per CU, products of one
-    // under the softmax of the other (32 sequences of 1k-8k 112.7 -> 111.5 us,
-    // one of 2048 26.7 -> 24.7 us); fewer rows are not faster for it (54 rows
-    // 27.5 against 27.7 us, 6 rows 24.3 against 27.3 us)
-    pl.per_cu = !pl.pc && pl.nw == 4 ? 2 : 1;
-    pl.grid = device_cus() * pl.per_cu;
+    // (512 shares at 97 .. 128 rows: 90.1 against 100.6 us for 32 sequences of
+    // 1k-8k, but more rows then pass through bf16 partials: relative error
+    // 2.9e-3 against 2.8e-3, not kept)
+    pl.grid = device_cus();
   } else {
     int C = chunk_keys > 0 ? chunk_keys : 4096;
     pl.chunk_tiles = C / KT;
@@ -1999,7 +1997,7 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     // output elements per item) or an item is split over many workgroups (8),
     // and the page table can hold a split worth it (the lengths are not known
     // here).  In-kernel count-in and merge against the launch, us: 32 x 128
-    // rows of 128 dims 111.4 / 90.2; 1 x 128 rows 25.3 / 19.0; 20 x 68 rows of
+    // rows of 128 dims 111.4 / 90.2 (512 shares); 1 x 128 rows 25.3 / 19.0; 20 x 68 rows of
     // 64 dims 23.7 / 21.5; 4 items of 28 rows in 16 segments 28.9 / 25.6; an
     // AR step of 9 segments 823 / 814; but 28 items of 3 rows in 6 segments
     // 13.1 / 16.3, 204 items of 8 rows in one or two 44.3 / 46.2.
@@ -2055,7 +2053,10 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
     hipLaunchKernelGGL((attn_bf16_pc_kernel<D, 4>), gr, dim3(512), 0, st, prm);
     return;
   }
-  // (more than 128 rows take the producer/consumer kernel)
+  // (more than 128 rows take the producer/consumer kernel).  Four waves: two
+  // 64-key tiles in flight and at most 256 registers, so that two workgroups
+  // may share a CU (four tiles and 396 registers: 32 sequences of 1k-8k 115.2
+  // against 100.6 us, one of 2048 21.9 against 19.0 us)
   switch (pl.nw) {
     case 4: hipLaunchKernelGGL((attn_bf16_kernel<D, 4, true, D == 64 ? 4 : 2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
     case 2: hipLaunchKernelGGL((attn_bf16_kernel<D, 2, true, NSTAGE, 1>), gr, dim3(128), 0, st, ATTN_HEAD_ARGS(prm), prm); break;
