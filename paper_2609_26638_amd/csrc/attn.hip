@@ -1898,15 +1898,17 @@ __global__ void attn_merge_kernel(const int32_t* __restrict__ kv_len, int R, int
 }
 
 // Appends the window's K/V ([L, T)) to the pool, one workgroup per (64-key
-// tile, KV head, sequence): aligned calls of several row tiles, whose
+// tile, KV head, sequence), all in the x dimension (y and z end at 65535 and
+// a call may hold more sequences): aligned calls of several row tiles, whose
 // workgroups would otherwise each append the whole window again (8832 rows,
 // 18 window tiles, 35 row tiles of 4 KV heads: most of the launch's time).
 template <int D>
 __global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
-  const int s = blockIdx.z, kvh = blockIdx.y;
+  const int n_win = (p.R + KT - 1) / KT + 1;   // tiles a window can touch
+  const int sk = (int)blockIdx.x / n_win, s = sk / p.Hkv, kvh = sk - s * p.Hkv;
   const int L = p.kv_len[s], T = L + p.R;
   if (L < 0 || T > p.max_pages * 16) return;   // reported by the attention launch
-  const int j = L / KT + (int)blockIdx.x;
+  const int j = L / KT + (int)blockIdx.x - sk * n_win;
   const int a = max(L, j * KT), b = min(T, (j + 1) * KT);
   if (a >= b) return;
   const int32_t* __restrict__ pt = p.page_table + (size_t)s * p.max_pages;
@@ -2038,7 +2040,7 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
     constexpr int NST2 = D == 128 ? 2 : (D == 96 ? 3 : 4);
     prm.appended = pl.n_row_tiles > 1;
     if (prm.appended)
-      hipLaunchKernelGGL(attn_append_kernel<D>, dim3((prm.R + KT - 1) / KT + 1, prm.Hkv, prm.S), dim3(256), 0, st, prm);
+      hipLaunchKernelGGL(attn_append_kernel<D>, dim3((unsigned)((prm.R + KT - 1) / KT + 1) * prm.Hkv * prm.S), dim3(256), 0, st, prm);
     if constexpr (D == 128) {
       if (pl.per_cu == 2) hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, NST2, 2>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);
       else hipLaunchKernelGGL((attn_bf16_kernel<D, 4, false, 4, 1>), gr, dim3(256), 0, st, ATTN_HEAD_ARGS(prm), prm);

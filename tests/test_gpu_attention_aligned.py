@@ -85,3 +85,26 @@ def test_merge(lens, R, Hq, Hkv, D, chunk):
                                ai.as_f64("k_pool"), ai.as_f64("v_pool"), ai.state.page_table[:n],
                                ai.state.kv_len[:n], R, 0, ai.scale)
     assert max_rel_err(to_f64(outs[0][:n]), ref) <= 2e-2
+
+
+def test_more_sequences_than_a_grid_dimension():
+    """65,600 equal sequences of two row tiles: the append launch holds them all."""
+    S, R, Hq, Hkv, D, pages = 65600, 65, 2, 1, 64, 5
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def same(*shape):
+        x = torch.randn(1, *shape, generator=g, device="cuda").to(torch.bfloat16)
+        return x.expand(S, *shape).contiguous()
+
+    q, kn, vn = same(R, Hq, D), same(R, Hkv, D), same(R, Hkv, D)
+    kp = torch.zeros(S * pages, Hkv, 16, D, dtype=torch.bfloat16, device="cuda")
+    vp = torch.zeros(S * pages, Hkv, D, 16, dtype=torch.bfloat16, device="cuda")
+    pt = torch.arange(S * pages, dtype=torch.int32, device="cuda").view(S, pages)
+    lens = torch.zeros(S, dtype=torch.int32, device="cuda")
+    out = dvs.attn_hybrid_block(q, kn, vn, kp, vp, pt, lens, R, 0, D ** -0.5, chunk_keys=128)
+    one = dvs.attn_hybrid_block(q[:1], kn[:1], vn[:1], torch.zeros_like(kp[:pages]),
+                                torch.zeros_like(vp[:pages]), pt[:1], lens[:1], R, 0, D ** -0.5,
+                                chunk_keys=128)
+    assert torch.equal(out, one.expand_as(out))
+    k = kp.view(S, pages * 16, Hkv, D)[:, :R]
+    assert torch.equal(k, kn)
