@@ -1558,10 +1558,16 @@ static int gemm_f32(const void* A, F32Segs sg, int nseg, int M, int K, int accum
     if (i < nseg) nb += (sg.n[i] + 31) / 32;
     sg.nb[i] = nb;
   }
-  const long long nm = ((long long)M + 31) / 32;
-  DVS_CHECK_SUPPORTED(nm <= 65535, "draft_verify_step: fp32 GEMM of %d rows", M);
-  hipLaunchKernelGGL(gemm_f32_kernel, dim3(nb, (unsigned)nm), dim3(64), 0, st, (const float*)A, M, K,
-                     accumulate, sg);
+  // (a grid holds 65535 row tiles in y)
+  constexpr int MB = 65535 * 32;
+  for (int m0 = 0; m0 < M;) {
+    const int mr = std::min(M - m0, MB);
+    F32Segs sb = sg;
+    for (int i = 0; i < nseg; ++i) sb.C[i] += (size_t)m0 * sg.n[i];
+    hipLaunchKernelGGL(gemm_f32_kernel, dim3(nb, (unsigned)((mr + 31) / 32)), dim3(64), 0, st,
+                       (const float*)A + (size_t)m0 * K, mr, K, accumulate, sb);
+    m0 += mr;
+  }
   return launch_status("draft_verify_step(gemm)");
 }
 
