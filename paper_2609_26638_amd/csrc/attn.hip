@@ -1629,6 +1629,9 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
 // 72 -> 14 us; with one element per load and one wave over the 256 keys
 // before).
 // ---------------------------------------------------------------------------
+// (fp32 arrays need only the alignment of their elements: a tensor that
+// starts inside another one)
+typedef f32x4 f32x4_a4 __attribute__((aligned(4)));
 template <int D>
 __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
   constexpr int DE = (D + 63) / 64;   // head-dim elements per lane: lane, lane + 64
@@ -1702,7 +1705,7 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
           f32x4 x[DB / 4];
 #pragma unroll
           for (int d = 0; d < DB / 4; ++d)
-            if (d0 + 4 * d < D) x[d] = *(const f32x4*)(krow + d0 + 4 * d);
+            if (d0 + 4 * d < D) x[d] = *(const f32x4_a4*)(krow + d0 + 4 * d);
 #pragma unroll
           for (int d = 0; d < DB / 4; ++d)
             if (d0 + 4 * d < D) {
@@ -1754,7 +1757,7 @@ __global__ void __launch_bounds__(256) attn_f32_kernel(AttnParams p) {
           if (d < D) {
             f32x4 x[4];
 #pragma unroll
-            for (int c = 0; c < 4; ++c) x[c] = *(const f32x4*)(vrow + (size_t)d * 16 + 4 * c);
+            for (int c = 0; c < 4; ++c) x[c] = *(const f32x4_a4*)(vrow + (size_t)d * 16 + 4 * c);
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
               const f32x4 y = *(const f32x4*)(pj + 4 * c);

@@ -83,6 +83,21 @@ def test_attention_matches_oracle(case):
     np.testing.assert_array_equal(to_f64(d["v_pool"]), vp)
 
 
+def test_fp32_arrays_at_element_alignment():
+    """fp32 arrays that start one element into another tensor: the vector loads
+    see 4-byte aligned addresses and give the same bits."""
+    ai = synth.make_attn_inputs(47, 2, [300, 45], 4, 4, 8, 2, 64, "f32", scatter=True)
+    ref, _ = _run(ai, 0)
+    d = dev_attn(ai)
+    for f in ("q", "k_new", "v_new", "k_pool", "v_pool"):
+        buf = torch.empty(d[f].numel() + 1, dtype=torch.float32, device="cuda")
+        d[f] = buf[1:].view(d[f].shape).copy_(d[f])
+        assert d[f].data_ptr() % 16 == 4
+    out = dvs.attn_hybrid_block(**d, n_causal=4, n_mask=4, softmax_scale=ai.scale)
+    torch.cuda.synchronize()
+    assert torch.equal(out.view(torch.int32), ref.view(torch.int32))
+
+
 def test_deterministic_and_page_permutation_invariant():
     ai = synth.make_attn_inputs(31, 3, [700, 33, 1500], 16, 16, 16, 4, 128, "bf16", scatter=True)
     o1, _ = _run(ai, 256)
