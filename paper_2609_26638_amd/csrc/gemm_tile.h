@@ -26,8 +26,8 @@
 
 namespace dvs {
 
-// The epilogue of a tile of MT x CT summed values in LDS (fp32, row-major),
-// by NT threads.  Columns past the call's are skipped; a 32-column block lies
+// The bf16 and top-1 epilogues of a tile of MT x CT summed values in LDS (fp32,
+// row-major), by NT threads.  Columns past the call's are skipped; a 32-column block lies
 // in one segment.
 template <int MT, int CT, int NT, int EPI>
 __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, const float* __restrict__ s_sum,
@@ -142,47 +142,24 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, const float* __
       *(u32x2*)(dst + d2) = __builtin_bit_cast(u32x2, y2);
     }
   } else {
-    constexpr int UNITS = MT * CT / 4, UB = UNITS / NT < 8 ? UNITS / NT : 8;
-    static_assert(UNITS % (NT * UB) == 0, "whole batches");
-    for (int u0 = tid; u0 < UNITS; u0 += NT * UB) {
-      f32x4 old[UB];
-      if constexpr (EPI == EPI_F32_ADD) {
-        // the batch's residual values in flight together
+    static_assert(EPI == EPI_BF16, "fp32 results are stored by the kernel");
+    constexpr int UNITS = MT * CT / 4;
+    static_assert(UNITS % NT == 0, "whole rounds");
+#pragma unroll 8
+    for (int u = tid; u < UNITS; u += NT) {
+      const int r = u / (CT / 4), cc = (u % (CT / 4)) * 4;
+      const int row = m0 + r, gcol = c0 + cc;
+      const GemmSeg sg = g.seg[seg_of(gcol)];
+      const int col = gcol - sg.n0;
+      if (row >= g.M || col >= sg.n) continue;
+      const f32x4 t = *(const f32x4*)(s_sum + r * CT + cc);
+      __bf16* dst = (__bf16*)sg.C + (size_t)row * sg.n + col;
+      if ((sg.n & 3) == 0 && col + 4 <= sg.n) {
+        *(bf16x4*)dst = __builtin_convertvector(t, bf16x4);
+      } else {
 #pragma unroll
-        for (int j = 0; j < UB; ++j) {
-          const int u = u0 + j * NT;
-          const int r = u / (CT / 4), cc = (u % (CT / 4)) * 4;
-          const int row = min(m0 + r, g.M - 1), col = c0 + cc;
-          const GemmSeg sg = g.seg[0];
-          old[j] = f32x4{0.f, 0.f, 0.f, 0.f};
-          if ((sg.n & 3) == 0 && col + 4 <= sg.n)
-            old[j] = *(const f32x4*)((const float*)sg.C + (size_t)row * sg.n + col);
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < UB; ++j) {
-        const int u = u0 + j * NT;
-        if (u >= UNITS) break;
-        const int r = u / (CT / 4), cc = (u % (CT / 4)) * 4;
-        const int row = m0 + r, gcol = c0 + cc;
-        const GemmSeg sg = g.seg[EPI == EPI_BF16 ? seg_of(gcol) : 0];
-        const int col = gcol - sg.n0;
-        if (row >= g.M || col >= sg.n) continue;
-        const f32x4 t = *(const f32x4*)(s_sum + r * CT + cc);
-        const size_t o = (size_t)row * sg.n + col;
-        if ((sg.n & 3) == 0 && col + 4 <= sg.n) {
-          if constexpr (EPI == EPI_BF16) *(bf16x4*)((__bf16*)sg.C + o) = __builtin_convertvector(t, bf16x4);
-          else if constexpr (EPI == EPI_F32_ADD) *(f32x4*)((float*)sg.C + o) = old[j] + t;
-          else *(f32x4*)((float*)sg.C + o) = t;
-        } else {
-#pragma unroll
-          for (int i = 0; i < 4; ++i) {
-            if (col + i >= sg.n) break;
-            if constexpr (EPI == EPI_BF16) ((__bf16*)sg.C)[o + i] = (__bf16)t[i];
-            else if constexpr (EPI == EPI_F32_ADD) ((float*)sg.C)[o + i] += t[i];
-            else ((float*)sg.C)[o + i] = t[i];
-          }
-        }
+        for (int i = 0; i < 4; ++i)
+          if (col + i < sg.n) dst[i] = (__bf16)t[i];
       }
     }
   }
@@ -302,6 +279,30 @@ gemm_tile_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
       __builtin_amdgcn_sched_barrier(0);
     });
   };
+  // fp32 results are stored from the accumulators: 32 lanes write 128 bytes
+  // of a row, without the two barriers and the trip through LDS of the bf16
+  // epilogues, which regroup columns.  The residual's values come first of
+  // all where the registers allow, under the products (rows and columns past
+  // the end read the last one's).  Whole calls, through LDS -> from the
+  // accumulators: 1024-row step of four layers 1002 -> 987 us, 2176-row step
+  // with fp32 logits 1776 -> 1753 us, prefill of 8832 rows 2727 -> 2700 us.
+  // One workgroup per CU over several tiles, the next one's copies under the
+  // stores of the last, was slower than the dispatcher's rounds (1017, 1789,
+  // 2841 us).
+  constexpr bool ADD = EPI == EPI_F32_ADD, EARLY = ADD && RG * CG <= 2;
+  const int mw = m0 + wr * RG * 32 + 4 * hh, cw = c0 + wc * CG * 32 + l32;
+  float* __restrict__ C = ADD ? (float*)hW1 : (float*)g.seg[0].C;
+  f32x16 old[ADD ? RG : 1][ADD ? CG : 1];
+  auto load_old = [&]() {
+#pragma unroll
+    for (int a = 0; a < RG; ++a)
+#pragma unroll
+      for (int b = 0; b < CG; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          old[a][b][i] = C[(size_t)min(mw + a * 32 + 8 * (i >> 2) + (i & 3), M - 1) * ncols + min(cw + b * 32, ncols - 1)];
+  };
+  if constexpr (EARLY) load_old();
   static_for<0, NS>([&](auto c) {
     if (decltype(c)::value < nch) static_for<0, PW>([&](auto i) { issue_one(decltype(c)::value, decltype(c)::value, decltype(i)::value); });
   });
@@ -340,17 +341,37 @@ gemm_tile_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
 #pragma unroll
       for (int b = 0; b < CG; ++b) sum[a][b] += acc[a][b];
   }
-  __syncthreads();
-  float* s_sum = (float*)s_ring;
+  if constexpr (EPI == EPI_F32 || ADD) {
+    if constexpr (ADD && !EARLY) load_old();
 #pragma unroll
-  for (int a = 0; a < RG; ++a)
+    for (int a = 0; a < RG; ++a)
 #pragma unroll
-    for (int b = 0; b < CG; ++b)
+      for (int b = 0; b < CG; ++b) {
+        if constexpr (ADD) {
 #pragma unroll
-      for (int i = 0; i < 16; ++i)
-        s_sum[((wr * RG + a) * 32 + 8 * (i >> 2) + 4 * hh + (i & 3)) * CT + (wc * CG + b) * 32 + l32] = sum[a][b][i];
-  __syncthreads();
-  tile_epilogue<MT, CT, NT, EPI>(g, s_sum, tid, lane, m0, c0);
+          for (int i = 0; i < 16; ++i) sum[a][b][i] = old[a][b][i] + sum[a][b][i];
+          asm volatile("" : "+v"(sum[a][b]));   // (not one load at a time under the conditions below)
+        }
+        if (cw + b * 32 < ncols)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) {
+            const int row = mw + a * 32 + 8 * (i >> 2) + (i & 3);
+            if (row < M) C[(size_t)row * ncols + cw + b * 32] = sum[a][b][i];
+          }
+      }
+  } else {
+    __syncthreads();
+    float* s_sum = (float*)s_ring;
+#pragma unroll
+    for (int a = 0; a < RG; ++a)
+#pragma unroll
+      for (int b = 0; b < CG; ++b)
+#pragma unroll
+        for (int i = 0; i < 16; ++i)
+          s_sum[((wr * RG + a) * 32 + 8 * (i >> 2) + 4 * hh + (i & 3)) * CT + (wc * CG + b) * 32 + l32] = sum[a][b][i];
+    __syncthreads();
+    tile_epilogue<MT, CT, NT, EPI>(g, s_sum, tid, lane, m0, c0);
+  }
 }
 
 }  // namespace dvs

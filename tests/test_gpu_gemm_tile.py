@@ -73,12 +73,15 @@ def test_many_row_step_matches_oracle(H, Hq, Hkv, D, ffn, V, S, nc, nm):
     np.testing.assert_array_equal(am2, am)
 
 
-def test_rows_equal_the_few_row_kernels():
-    """520 rows in one call, then each of two sequences alone (40 rows)."""
-    S, nc, nm = 13, 20, 20
-    w, ai = _model(256, 4, 2, 64, 512, 33001, S, nc, nm)
+# 520 rows: the head has several tiles per workgroup, its last ones part
+# empty; 8320 rows x 1024: so has the residual, 260 tiles on 256 CUs.
+@pytest.mark.parametrize("S,H,Hq,Hkv,ffn,V", [(13, 256, 4, 2, 512, 33001), (208, 1024, 4, 2, 256, 1000)])
+def test_rows_equal_the_few_row_kernels(S, H, Hq, Hkv, ffn, V):
+    """All sequences in one call, then each of three alone (40 rows)."""
+    nc, nm = 20, 20
+    w, ai = _model(H, Hq, Hkv, 64, ffn, V, S, nc, nm)
     lg, am, _ = _step(w, ai, ai.state, nc, nm)
-    for s in (0, S - 1):
+    for s in (0, S // 2, S - 1):
         h = ai.state.copy()
         for f in ("kv_len", "page_table", "num_pages", "boundary", "draft", "out_tokens",
                   "out_count", "finished"):
