@@ -1922,6 +1922,7 @@ __global__ void __launch_bounds__(256) attn_append_kernel(AttnParams p) {
 struct AttnPlan {
   int nw, rows_total, rows_per_wg, n_row_tiles, n_items, balanced, pc;
   int chunk_tiles, n_chunks_max, wgs_per_item, xcd_run, merge_launch, per_cu, share_min, max_segs, grid;
+  int counted;   // the call uses its counters
   size_t off_counters, off_meta, off_ml, off_o, bytes;
 };
 
@@ -2010,10 +2011,12 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     const int segs = std::min(segs_max, pl.grid / std::max(1, pl.n_items));
     pl.merge_launch = !pl.pc && segs_max >= MERGE_MIN_SEGS && (pl.balanced || pl.wgs_per_item > 1) &&
                       (pl.rows_total * D > MERGE_MIN_ELEMS || segs >= MERGE_MANY_SEGS);
+    // Every shape keeps a counter per item at the front, also where none is
+    // counted in (a launch merges, or one workgroup holds every chunk of its
+    // item): partials written there would be another shape's counters.
+    pl.counted = !pl.merge_launch && (pl.balanced || pl.wgs_per_item > 1);
     pl.off_counters = 0;
-    // (no counters where one workgroup holds every chunk of its item)
-    const bool counted = pl.balanced || pl.wgs_per_item > 1;
-    pl.off_meta = counted ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0;
+    pl.off_meta = align256((size_t)pl.n_items * sizeof(int32_t));
     pl.off_ml = pl.off_meta +
                 (pl.merge_launch && pl.balanced ? align256((size_t)pl.n_items * sizeof(int32_t)) : 0);
     pl.off_o = pl.off_ml + align256(slots * ml_b);
@@ -2075,7 +2078,7 @@ size_t attn_counter_bytes(int S, int R, int Hq, int Hkv, int D, int max_pages, i
                           int dtype) {
   if (dtype != DVS_BF16) return 0;
   const AttnPlan pl = plan_attn(S, R, Hq, Hkv, D, max_pages, chunk_keys, dtype);
-  return pl.off_meta - pl.off_counters;
+  return pl.counted ? pl.off_meta - pl.off_counters : 0;
 }
 
 }  // namespace dvs
@@ -2152,10 +2155,10 @@ static int attn_launch(const void* q, const void* k_new, const void* v_new, void
     prm.part_ml = (float*)(ws + pl.off_ml);
     prm.part_o = (float*)(ws + pl.off_o);
     DVS_CHECK_SUPPORTED((long long)pl.grid < (1LL << 31), "attn_hybrid_block: grid too large");
-    if (scratch_cap > 0) {
+    if (scratch_cap > 0 && pl.counted) {
       // the array keeps the previous call's contents: clear the counters
       const int nw = (int)((pl.off_meta - pl.off_counters) / sizeof(int32_t));
-      if (nw) hipLaunchKernelGGL(attn_zero_kernel, dim3((nw + 255) / 256), dim3(256), 0, st, prm.counters, nw);
+      hipLaunchKernelGGL(attn_zero_kernel, dim3((nw + 255) / 256), dim3(256), 0, st, prm.counters, nw);
     }
     if (D == 128) launch_bf16<128>(pl, prm, st);
     else if (D == 96) launch_bf16<96>(pl, prm, st);

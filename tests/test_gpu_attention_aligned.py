@@ -87,6 +87,37 @@ def test_merge(lens, R, Hq, Hkv, D, chunk):
     assert max_rel_err(to_f64(outs[0][:n]), ref) <= 2e-2
 
 
+class _NeverCleared(dvs.Workspace):
+    def prepare(self, nbytes, shape):
+        assert nbytes <= self.nbytes
+        return self
+
+
+# A workspace zeroed once serves other shapes whose counters lie in those of
+# the first: a call of many items whose chunks stay in one workgroup (it counts
+# nothing in), one merged by a launch (balanced, with its segment table), then
+# a small one that counts in.
+def test_shapes_share_the_workspace_counters():
+    many = synth.make_attn_inputs(21, 8, [300, 64, 200, 5, 0, 17, 0, 90], 512, 0, 16, 4, 64, "bf16",
+                                  std=1.0, scatter=True)
+    split = synth.make_attn_inputs(22, 4, [1500, 30, 700, 64], 30, 0, 16, 4, 64, "bf16", std=1.0,
+                                   scatter=True)
+    small = synth.make_attn_inputs(23, 2, [500, 190], 3, 0, 8, 4, 64, "bf16", std=1.0, scatter=True)
+    calls = [(many, 128), (small, 128), (split, 0), (small, 128), (many, 128), (split, 0)]
+
+    def call(ai, chunk, ws):
+        d = dev_attn(ai)
+        nc = ai.q.shape[1]
+        return dvs.attn_hybrid_block(d["q"], d["k_new"], d["v_new"], d["k_pool"], d["v_pool"],
+                                     d["page_table"], d["kv_len"], nc, 0, ai.scale, workspace=ws,
+                                     chunk_keys=chunk)
+
+    ws = _NeverCleared(1 << 28)
+    for i, (ai, chunk) in enumerate(calls):
+        own = call(ai, chunk, None)
+        assert torch.equal(call(ai, chunk, ws), own), i
+
+
 def test_more_sequences_than_a_grid_dimension():
     """65,600 equal sequences of two row tiles: the append launch holds them all."""
     S, R, Hq, Hkv, D, pages = 65600, 65, 2, 1, 64, 5
