@@ -88,6 +88,21 @@ __device__ __forceinline__ size_t part_slot(int balanced, int it, int max_segs, 
   return balanced ? (size_t)(wg0 + k) * 2 + (k == 0 ? 1 : 0) : (size_t)it * max_segs + k;
 }
 
+// One segment of a merge: its weight exp2(m - M) l, added to the item's l, and
+// a word of two bf16 elements of its O / l, added to the item's O.  The
+// attention kernel and attn_merge_kernel share these, with the contractions
+// written out: which of them merges an item depends on the batch, and a row's
+// bits must not.
+__device__ __forceinline__ float merge_weight(f32x2 ml, float M, float& l) {
+  const float e = __builtin_amdgcn_exp2f(ml[0] - M);
+  l = fmaf(e, ml[1], l);
+  return e * ml[1];
+}
+__device__ __forceinline__ void merge_add(uint32_t w, float wgt, float& o0, float& o1) {
+  o0 = fmaf(wgt, __uint_as_float(w << 16), o0);
+  o1 = fmaf(wgt, __uint_as_float(w & 0xffff0000u), o1);
+}
+
 struct AttnParams {
   const void* q;
   const void* k_new;
@@ -898,16 +913,16 @@ attn_bf16_kernel(const int32_t* __restrict__ kv_len, const int32_t* __restrict__
 #pragma unroll
       for (int b = 0; b < SB; ++b) {
         if (c0 + b >= nseg) break;
-        const float wgt = __builtin_amdgcn_exp2f(mlc[b][0] - Ms) * mlc[b][1];
-        lt += wgt;
+        const float wgt = merge_weight(mlc[b], Ms, lt);
 #pragma unroll
         for (int jw = 0; jw < NWD; ++jw)
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
             const int f0 = 8 * jw + 2 * e;
-            const uint32_t wd = pv[b][jw][e];
-            acc[f0 / 16][f0 % 16] += wgt * __uint_as_float(wd << 16);
-            acc[(f0 + 1) / 16][(f0 + 1) % 16] += wgt * __uint_as_float(wd & 0xffff0000u);
+            float a0 = acc[f0 / 16][f0 % 16], a1 = acc[(f0 + 1) / 16][(f0 + 1) % 16];
+            merge_add(pv[b][jw][e], wgt, a0, a1);
+            acc[f0 / 16][f0 % 16] = a0;
+            acc[(f0 + 1) / 16][(f0 + 1) % 16] = a1;
           }
       }
     }
@@ -1877,13 +1892,9 @@ __global__ void attn_merge_kernel(const int32_t* __restrict__ kv_len, int R, int
 #pragma unroll
     for (int b = 0; b < SB; ++b) {
       if (c0 + b >= nseg) break;
-      const float wgt = __builtin_amdgcn_exp2f(mlc[b][0] - Ms) * mlc[b][1];
-      lt += wgt;
+      const float wgt = merge_weight(mlc[b], Ms, lt);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        acc[2 * e] += wgt * __uint_as_float(pv[b][e] << 16);
-        acc[2 * e + 1] += wgt * __uint_as_float(pv[b][e] & 0xffff0000u);
-      }
+      for (int e = 0; e < 4; ++e) merge_add(pv[b][e], wgt, acc[2 * e], acc[2 * e + 1]);
     }
   }
   const float inv = lt > 0.f ? 1.f / lt : 0.f;

@@ -87,6 +87,26 @@ def test_merge(lens, R, Hq, Hkv, D, chunk):
     assert max_rel_err(to_f64(outs[0][:n]), ref) <= 2e-2
 
 
+# A row's bits do not depend on who merges its chunks: a launch (alone), the
+# last workgroup to count in (20 sequences, seven workgroups per item), or the
+# only workgroup (130 sequences).
+@pytest.mark.parametrize("D", [64, 96, 128])
+def test_merges_have_the_same_bits(D):
+    lens = [700, 641, 900, 577] + [(37 * s) % 800 for s in range(126)]
+    ai = synth.make_attn_inputs(19, len(lens), lens, 1, 0, 8, 4, D, "bf16", std=1.0, scatter=True)
+    d = dev_attn(ai)
+    outs = []
+    for n in (1, 20, 130):
+        a = {f: x if f.endswith("pool") else x[:n] for f, x in d.items()}
+        outs.append(dvs.attn_hybrid_block(**a, n_causal=1, n_mask=0, softmax_scale=ai.scale,
+                                          chunk_keys=64))
+    assert torch.equal(outs[0], outs[1][:1]) and torch.equal(outs[1], outs[2][:20])
+    for s in (1, 2, 3):   # and the others alone
+        a = {f: x if f.endswith("pool") else x[s:s + 1] for f, x in d.items()}
+        one = dvs.attn_hybrid_block(**a, n_causal=1, n_mask=0, softmax_scale=ai.scale, chunk_keys=64)
+        assert torch.equal(one[0], outs[2][s]), s
+
+
 class _NeverCleared(dvs.Workspace):
     def prepare(self, nbytes, shape):
         assert nbytes <= self.nbytes
