@@ -521,9 +521,10 @@ struct GemmArgs {
 // they were a chain of loads from memory in front of every launch's stream.
 // n1, n2: first column of segments 1 and 2 (past every column if absent); for
 // EPI_SWIGLU n1 is the number of gate (and up) rows; for EPI_F32_ADD (one
-// segment) hW1 is the residual array.
+// segment) hW1 is the residual array, which the epilogue also writes (so hW1
+// is not __restrict__).
 #define GEMM_HEAD_PARAMS                                                                          \
-  const __bf16 *__restrict__ hA, const __bf16 *__restrict__ hW0, const __bf16 *__restrict__ hW1,  \
+  const __bf16 *__restrict__ hA, const __bf16 *__restrict__ hW0, const __bf16 *hW1,               \
       const __bf16 *__restrict__ hW2, int K, int M, int n_rt, int ncols, int n1, int n2, int rope_D
 #define GEMM_HEAD_ARGS(g)                                                                         \
   (g).A, (g).seg[0].W, (g).epi == EPI_F32_ADD ? (const __bf16*)(g).seg[0].C : (g).seg[1].W,       \
