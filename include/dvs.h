@@ -320,7 +320,8 @@ int kv_commit_round(int32_t S, int32_t B, const int32_t* lead, const int32_t* ac
  *
  * Weights are row-major [out_features, in_features]; all live in device
  * memory, in the model dtype (DVS_F32 or DVS_BF16; fp32 accumulation, fp32
- * residual stream, fp32 logits).  A row's arithmetic does not depend on how
+ * residual stream, fp32 logits), at the alignment of their elements (bf16
+ * ones that start on 16 bytes take the faster copies).  A row's arithmetic does not depend on how
  * many rows the call carries, so AR and fused calls agree bit for bit on the
  * causal rows (for the attention this needs chunk_keys > 0).
  *

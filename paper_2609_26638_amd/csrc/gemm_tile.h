@@ -26,6 +26,8 @@
 
 namespace dvs {
 
+typedef u32x4 u32x4_a2 __attribute__((aligned(2)));
+
 // The bf16 and top-1 epilogues of a tile of MT x CT summed values in LDS (fp32,
 // row-major), by NT threads.  Columns past the call's are skipped; a 32-column block lies
 // in one segment.
@@ -165,7 +167,10 @@ __device__ __forceinline__ void tile_epilogue(const GemmArgs& g, const float* __
   }
 }
 
-template <int WM, int WN, int RG, int CG, int NS, int EPI>
+// ALIGNED = false: operands that do not all start on 16 bytes (a weight that
+// begins inside another tensor).  Direct global -> LDS copies are only used on
+// 16-byte addresses; these go through registers, by loads of any alignment.
+template <int WM, int WN, int RG, int CG, int NS, int EPI, bool ALIGNED = true>
 __global__ void __launch_bounds__(WM * WN * 64, (NS * (WM * RG + WN * CG) * 4096 <= 81920 && WM * WN == 4) ? 2 : 1)
 gemm_tile_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   constexpr int NW = WM * WN, NT = NW * 64;
@@ -231,8 +236,11 @@ gemm_tile_kernel(GEMM_HEAD_PARAMS, GemmArgs g) {
   const int nch = K / KC;
   const int cps = nch / g.ksplit;                        // chunks per split
   auto issue_one = [&](int t, int slot, int i) {         // copy i of the wave's PW copies of chunk t
-    __builtin_amdgcn_global_load_lds((const void*)(src[i] + t * KC),
-                                     (__attribute__((address_space(3))) void*)(s_ring + slot * STB + (w * PW + i) * 1024), 16, 0, 0);
+    char* dst = s_ring + slot * STB + (w * PW + i) * 1024;
+    if constexpr (ALIGNED)
+      __builtin_amdgcn_global_load_lds((const void*)(src[i] + t * KC), (__attribute__((address_space(3))) void*)dst, 16, 0, 0);
+    else
+      *(u32x4*)(dst + lane * 16) = *(const u32x4_a2*)(src[i] + t * KC);
   };
   const int wr = w / WN, wc = w % WN;
   // Fragments are read half a chunk (two 16-k steps) ahead of their products:

@@ -1388,7 +1388,7 @@ static StepLayout step_layout(const dvs_model* m, int S, int n_causal, int n_mas
   return L;
 }
 
-template <int WM, int WN, int RG, int CG, int NS>
+template <int WM, int WN, int RG, int CG, int NS, bool ALIGNED = true>
 static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
   constexpr int MT = WM * RG * 32, CT = WN * CG * 32;
   g.n_rt = (g.M + MT - 1) / MT;
@@ -1396,11 +1396,11 @@ static int launch_tile_cfg(GemmArgs& g, hipStream_t st) {
   DVS_CHECK_SUPPORTED(total < (1LL << 30), "draft_verify_step: GEMM grid too large");
   const dim3 gr((unsigned)((total + 7) / 8 * 8)), blk(WM * WN * 64);
   switch (g.epi) {
-    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
-    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
-    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
-    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
-    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_BF16: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_BF16, ALIGNED>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32, ALIGNED>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_F32_ADD: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_F32_ADD, ALIGNED>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_SWIGLU: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_SWIGLU, ALIGNED>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    default: hipLaunchKernelGGL((gemm_tile_kernel<WM, WN, RG, CG, NS, EPI_ARGMAX, ALIGNED>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
   }
   return launch_status("draft_verify_step(gemm)");
 }
@@ -1549,6 +1549,12 @@ static bool use_ws(int M, int K) { return K % (64 * GK_SPLITS) == 0 && M <= WS_M
 
 static int launch_gemm(GemmArgs& g, hipStream_t st) {
   g.ksplit = gemm_ksplit(g.K);
+  // The kernels copy whole 16-byte pieces straight into LDS, rows of A and W
+  // being multiples of 128 bytes; where an operand starts off that, the form
+  // that goes through registers (the same bits at every size).
+  uintptr_t starts = (uintptr_t)g.A;
+  for (int i = 0; i < g.nseg; ++i) starts |= (uintptr_t)g.seg[i].W;
+  if (starts & 15) return launch_tile_cfg<2, 2, 1, 1, 4, false>(g, st);
   return use_ws(g.M, g.K) ? launch_ws(g, st) : launch_tile(g, st);
 }
 

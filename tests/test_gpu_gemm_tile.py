@@ -28,13 +28,30 @@ def _model(H, Hq, Hkv, D, ffn, V, S, nc, nm):
     return w, ai
 
 
-def _step(w, ai, host, nc, nm):
+def _shift(dm, shift):
+    """The GEMMs' weights start ``shift`` elements into another tensor."""
+    def moved(t):
+        buf = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")
+        return buf[shift:].view(t.shape).copy_(t)
+
+    dm.lm_head = moved(dm.lm_head)
+    dm.desc.lm_head = dm.lm_head.data_ptr()
+    for l, t in enumerate(dm.keep):
+        for n in ("wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"):
+            t[n] = moved(t[n])
+            setattr(dm.layers[l], n, t[n].data_ptr())
+            assert t[n].data_ptr() % 16 == shift * 2 % 16
+
+
+def _step(w, ai, host, nc, nm, shift=0):
     """(logits [S, R, V], top-1 with the logits, top-1 without)"""
     S, R = host.kv_len.shape[0], nc + nm
     lg = torch.empty((S, R, w.V), dtype=torch.float32, device="cuda")
     ams = []
     for logits in (lg, None):
         dm = dvs.DeviceModel(w, [to_dev(ai.k_pool, "bf16")], [to_dev(ai.v_pool, "bf16")], "bf16")
+        if shift:
+            _shift(dm, shift)
         st = dvs.DeviceState(host)
         am = torch.empty((S, R), dtype=torch.int32, device="cuda")
         dvs.draft_verify_step(dm, st, nc, nm, logits_out=logits, argmax_out=am)
@@ -89,3 +106,18 @@ def test_rows_equal_the_few_row_kernels(S, H, Hq, Hkv, ffn, V):
         one, am1, _ = _step(w, ai, h, nc, nm)
         np.testing.assert_array_equal(one[0], lg[s])
         np.testing.assert_array_equal(am1[0], am[s])
+
+
+# Weights at element alignment, of one and of four K splits, few rows and many.
+@pytest.mark.parametrize("H,Hq,Hkv,D,ffn,V,S,nc,nm,shift", [
+    (320, 5, 1, 64, 448, 1000, 1, 257, 0, 1),
+    (192, 2, 2, 96, 192, 515, 2, 2, 1, 4),
+    (256, 2, 1, 128, 512, 5000, 13, 40, 0, 1),
+    (256, 4, 2, 64, 512, 33001, 2, 20, 20, 2),
+])
+def test_weights_at_element_alignment(H, Hq, Hkv, D, ffn, V, S, nc, nm, shift):
+    w, ai = _model(H, Hq, Hkv, D, ffn, V, S, nc, nm)
+    ref = _step(w, ai, ai.state, nc, nm)
+    got = _step(w, ai, ai.state, nc, nm, shift)
+    for a, b in zip(got, ref):
+        np.testing.assert_array_equal(a, b)
