@@ -69,11 +69,7 @@ constexpr int NSTAGE = 4;              // LDS ring depth of the balanced split
 constexpr int SUB_TILES = 256;         // tiles whose page ids are staged at once
 constexpr int MAX_CHUNK_KEYS = 16384;
 constexpr int BAL_MAX_SEGS = 16;       // balanced mode: segments per item (bound)
-// Merge launches (attn_merge_kernel): output elements of an item, or segments
-// per item, from which on they pay; and the segments its page table must hold.
-constexpr int MERGE_MIN_ELEMS = 4096;
-constexpr int MERGE_MANY_SEGS = 8;
-constexpr int MERGE_MIN_SEGS = 4;
+constexpr int MERGE_MIN_ELEMS = 4096;  // output elements of an item that a launch merges
 constexpr int BAL_MAX_SEQS = 1024;     // balanced mode: sequences per call
 constexpr float RESCALE_LOG2 = 8.f;
 
@@ -2011,17 +2007,29 @@ static AttnPlan plan_attn(int S, int R, int Hq, int Hkv, int D, int max_pages, i
     const size_t o_b = pl.pc ? (size_t)256 * (2 * (D / 32) * 16) * 2
                              : (size_t)NT * (D / 32) * 16 * 2;
     // A launch of its own merges where the partials are many (more than 4096
-    // output elements per item) or an item is split over many workgroups (8),
-    // and the page table can hold a split worth it (the lengths are not known
-    // here).  In-kernel count-in and merge against the launch, us: 32 x 128
-    // rows of 128 dims 111.4 / 90.2 (512 shares); 1 x 128 rows 25.3 / 19.0; 20 x 68 rows of
-    // 64 dims 23.7 / 21.5; 4 items of 28 rows in 16 segments 28.9 / 25.6; an
-    // AR step of 9 segments 823 / 814; but 28 items of 3 rows in 6 segments
-    // 13.1 / 16.3, 204 items of 8 rows in one or two 44.3 / 46.2.
+    // output elements per item) or an item is split over many workgroups.  It
+    // costs its 1.6 - 2.0 us also while the caches are short and nothing is
+    // split (the lengths are not known here), so the page table must hold a
+    // split whose merge saves more than that on the average over its fill;
+    // mean gain over fills of 5, 25, 50, 75 and 100%, us:
+    //   aligned, many elements: tables of 4 chunks -1.6 .. 0.3, but with two
+    //     workgroups per CU counting in 1.0 .. 3.2 and, 128 dims wide, with
+    //     more than one 0.5 .. 0.7; 5 chunks -0.5 .. 4.3; 12 chunks 0.2 .. 6.6
+    //     (of 12 - 40);
+    //   aligned, few elements: 8 segments -0.6 .. 0.4; 9 -0.3 .. 2.3; 16
+    //     0.2 .. 5.2;
+    //   balanced, many elements: tables of 4 tiles -1.0 .. 4.3, 8 -0.3 .. 7.8;
+    //   balanced, few elements, 16 to 64 tiles: one sequence -1.1 .. 5.0,
+    //     8 sequences 1.1 .. 6.5.
+    // (Ends of one shape, 8 sequences of 1 row, D = 128, 16 chunks: 3% full
+    // 2.1 lost, full 13.0 saved.)
     const int segs_max = pl.balanced ? std::min(BAL_MAX_SEGS, max_tiles) : pl.n_chunks_max;
     const int segs = std::min(segs_max, pl.grid / std::max(1, pl.n_items));
-    pl.merge_launch = !pl.pc && segs_max >= MERGE_MIN_SEGS && (pl.balanced || pl.wgs_per_item > 1) &&
-                      (pl.rows_total * D > MERGE_MIN_ELEMS || segs >= MERGE_MANY_SEGS);
+    const bool many_wgs = D == 128 ? pl.grid > device_cus() : pl.grid >= 2 * device_cus();
+    const int table_segs = pl.balanced || many_wgs ? 4 : 5;
+    const int many_segs = pl.balanced ? 8 : 9;
+    pl.merge_launch = !pl.pc && segs_max >= table_segs && (pl.balanced || pl.wgs_per_item > 1) &&
+                      (pl.rows_total * D > MERGE_MIN_ELEMS || segs >= many_segs);
     // Every shape keeps a counter per item at the front, also where none is
     // counted in (a launch merges, or one workgroup holds every chunk of its
     // item): partials written there would be another shape's counters.
