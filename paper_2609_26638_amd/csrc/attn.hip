@@ -2063,7 +2063,16 @@ static void launch_bf16(const AttnPlan& pl, AttnParams& prm, hipStream_t st) {
   if (!pl.balanced) {
     // ring stages: what one or two workgroups per CU leave room for
     constexpr int NST2 = D == 128 ? 2 : (D == 96 ? 3 : 4);
-    prm.appended = pl.n_row_tiles > 1;
+    // Two row tiles that each append what they read hide it under their first
+    // copies while the window is a tile or two; a launch of its own costs 2 us
+    // first (us, launch / in the kernel; G rows per window row):
+    //   136 rows: G = 4 16.1 / 13.7 and 24.5 / 21.0, G = 2 (R = 68) 25.4 / 22.3
+    //     (22.8 with 8 waves per workgroup and the append in the kernel);
+    //   256 rows: G = 4 (R = 64) 27.0 / 24.0, G = 2 (R = 128) 35.2 / 37.5 and
+    //     40.0 / 38.1, G = 1 35.7 / 38.8;
+    //   384 and 512 rows (three and four row tiles), G = 4: D = 96 36.8 / 30.6,
+    //     D = 128 30.8 / 32.7 and 96.0 / 104.1; G = 1 57.9 / 68.8.
+    prm.appended = pl.n_row_tiles > 2 || (pl.n_row_tiles == 2 && prm.R > 96);
     if (prm.appended)
       hipLaunchKernelGGL(attn_append_kernel<D>, dim3((unsigned)((prm.R + KT - 1) / KT + 1) * prm.Hkv * prm.S), dim3(256), 0, st, prm);
     if constexpr (D == 128) {

@@ -37,6 +37,8 @@ def _call(d, s, nc, nm, group, scale, chunk):
     ([500, 190], 8, 64, 8, 16, 4, 96, 128),
     ([500, 190, 3], 12, 144, 12, 8, 2, 128, 64),
     ([0, 63, 64, 255, 256, 1500], 1, 0, 0, 4, 1, 96, 256),
+    ([700, 65, 0, 1000], 40, 24, 0, 16, 4, 64, 128),     # two row tiles, each appending
+    ([300, 17, 64], 150, 50, 0, 4, 4, 64, 64),           # two row tiles, an append launch
 ])
 def test_aligned_chunks(lens, nc, nm, group, Hq, Hkv, D, chunk):
     S = len(lens)
