@@ -1426,14 +1426,19 @@ static int launch_tile(GemmArgs& g, hipStream_t st) {
 template <int MT, int CWT, int CB, bool WK, bool FEW>
 static void launch_ws_epi(const GemmArgs& g, dim3 gr, hipStream_t st) {
   const dim3 blk(256);
+  // launch_ws gives 64-row calls of more than one workgroup per CU to
+  // gemm_nk_kernel (bf16, single blocks) and gemm_tile_kernel (gate|up, pairs)
+  constexpr bool BF16 = !(MT == 64 && CB == 1 && !WK), SWIGLU = !(MT == 64 && CB == 2 && !WK);
   switch (g.epi) {
-    case EPI_BF16: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_BF16, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
+    case EPI_BF16:
+      if constexpr (BF16) hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_BF16, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
+      break;
     case EPI_F32: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
     case EPI_F32_ADD: hipLaunchKernelGGL((gemm_ws_kernel<MT, CWT, CB, EPI_F32_ADD, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g); break;
     default:
       if constexpr (CWT == 32) {
-        if (g.epi == EPI_SWIGLU) hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_SWIGLU, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
-        else hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_ARGMAX, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
+        if (g.epi == EPI_ARGMAX) hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_ARGMAX, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
+        else if constexpr (SWIGLU) hipLaunchKernelGGL((gemm_ws_kernel<MT, 32, CB, EPI_SWIGLU, WK, FEW>), gr, blk, 0, st, GEMM_HEAD_ARGS(g), g);
       }
       break;
   }
