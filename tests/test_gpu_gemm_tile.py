@@ -1,8 +1,9 @@
 """GPU: the many-row decoder GEMM (gemm_tile_kernel) through
-draft_verify_step -- every tile size and epilogue, rows and columns that end
-inside a tile, K with one and with four logical splits -- against the float64
-oracle, its fused top-1 against the logits, and its rows bit for bit against
-the few-row kernels'."""
+draft_verify_step: against the float64 oracle (64 x 64 tiles for the layer,
+every tile size for the head; rows and columns that end inside a tile; K with
+one and with four logical splits), its fused top-1 against the logits, and at
+every tile size and epilogue its rows bit for bit against the few-row
+kernels'."""
 import dataclasses
 
 import numpy as np
@@ -90,22 +91,37 @@ def test_many_row_step_matches_oracle(H, Hq, Hkv, D, ffn, V, S, nc, nm):
     np.testing.assert_array_equal(am2, am)
 
 
-# 520 rows: the head has several tiles per workgroup, its last ones part
-# empty; 8320 rows x 1024: so has the residual, 260 tiles on 256 CUs.
-@pytest.mark.parametrize("S,H,Hq,Hkv,ffn,V", [(13, 256, 4, 2, 512, 33001), (208, 1024, 4, 2, 256, 1000)])
-def test_rows_equal_the_few_row_kernels(S, H, Hq, Hkv, ffn, V):
-    """All sequences in one call, then each of three alone (40 rows)."""
-    nc, nm = 20, 20
-    w, ai = _model(H, Hq, Hkv, 64, ffn, V, S, nc, nm)
-    lg, am, _ = _step(w, ai, ai.state, nc, nm)
+# Sequences, causal and mask rows each, hidden, heads, kv heads, head dim, ffn,
+# vocab.  520 rows: 64 x 64 tiles for the layer at every head dim (the rotary
+# epilogue), alone 40 rows or the narrow blocks' 10, the head in 128 x 256
+# tiles, alone in the column-split kernel; 240 rows: gate|up in 128 x 64 tiles
+# and Q|K|V in the row-split kernel; 1040 rows: Q|K|V and gate|up in 128 x 128
+# tiles; 2200 rows: the residual in those; 8320 rows: all in 128 x 256 tiles,
+# the last ones part empty.
+@pytest.mark.parametrize("S,nc,nm,H,Hq,Hkv,D,ffn,V", [
+    (13, 20, 20, 256, 4, 2, 64, 512, 33001),
+    (13, 20, 20, 256, 4, 2, 96, 512, 5000),
+    (52, 5, 5, 256, 2, 1, 128, 512, 5000),
+    (6, 20, 20, 256, 16, 4, 96, 4096, 33001),
+    (26, 20, 20, 256, 16, 4, 96, 1152, 5000),
+    (55, 20, 20, 1536, 4, 2, 64, 256, 1000),
+    (208, 20, 20, 1024, 4, 2, 64, 256, 1000),
+])
+def test_rows_equal_the_few_row_kernels(S, nc, nm, H, Hq, Hkv, D, ffn, V):
+    """All sequences in one call, then each of three alone, with the logits
+    and with the fused top-1 alone."""
+    w, ai = _model(H, Hq, Hkv, D, ffn, V, S, nc, nm)
+    lg, am, top = _step(w, ai, ai.state, nc, nm)
+    np.testing.assert_array_equal(top, am)
     for s in (0, S // 2, S - 1):
         h = ai.state.copy()
         for f in ("kv_len", "page_table", "num_pages", "boundary", "draft", "out_tokens",
                   "out_count", "finished"):
             setattr(h, f, getattr(h, f)[s:s + 1].copy())
-        one, am1, _ = _step(w, ai, h, nc, nm)
+        one, am1, top1 = _step(w, ai, h, nc, nm)
         np.testing.assert_array_equal(one[0], lg[s])
         np.testing.assert_array_equal(am1[0], am[s])
+        np.testing.assert_array_equal(top1[0], am[s])
 
 
 # Weights at element alignment, of one and of four K splits, few rows and many.

@@ -262,9 +262,9 @@ def test_bf16_wide_step_matches_oracle_replay():
     """A one-layer bf16 step at 256 window rows (8 sequences, B=16) whose
     projections take the wide decode-step GEMM paths: Q|K|V of 32/4 heads of
     64 (80 column blocks: the row-split 2x2 kernel with the rotary epilogue),
-    SwiGLU 2192 (137 gate|up blocks: the block-split 2x2 kernel, the last
-    pair half empty) and vocabulary 8200 (257 blocks: the column-split LM
-    head, the last block 8 columns wide). Logits close to the float64
+    SwiGLU 2192 (137 gate|up blocks: the many-row kernel's 128 x 64 tiles,
+    the last one half empty) and vocabulary 8200 (257 blocks: its wider tiles,
+    the last block 8 columns wide). Logits close to the float64
     oracle; the top-1 of the fused LM-head epilogue equals the top-1 of the
     logits; accept and commit replayed through the oracle bit for bit."""
     B, S = 16, 8
