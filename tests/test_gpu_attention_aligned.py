@@ -39,6 +39,12 @@ def _call(d, s, nc, nm, group, scale, chunk):
     ([0, 63, 64, 255, 256, 1500], 1, 0, 0, 4, 1, 96, 256),
     ([700, 65, 0, 1000], 40, 24, 0, 16, 4, 64, 128),     # two row tiles, each appending
     ([300, 17, 64], 150, 50, 0, 4, 4, 64, 64),           # two row tiles, an append launch
+    # 516 items of four row tiles: one workgroup streams all of an item's chunks
+    # (up to five) and merges its own partials; the XCDs' last run is short
+    ([0, 500, 250, 401] + [(83 * s) % 520 for s in range(39)], 60, 40, 0, 12, 3, 64, 128),
+    # 516 items again, one of 87 chunks: its page ids are staged a second time
+    # 256 tiles on, inside a chunk of three tiles
+    ([16500, 200, 0, 64] + [30] * 125, 2, 1, 0, 8, 4, 64, 192),
 ])
 def test_aligned_chunks(lens, nc, nm, group, Hq, Hkv, D, chunk):
     S = len(lens)
