@@ -21,7 +21,8 @@
 //     O^T[d, row] += V^T P^T  A = V^T slice of the head-dim-major V tile,
 //                             B = P packed to bf16 straight from the scores.
 //   A workgroup first appends the window keys of its own tiles ([L, T) from
-//   k_new / v_new) to their pool slots; then every tile, cache or window, is
+//   k_new / v_new) to their pool slots (long windows over several row tiles
+//   have a launch of their own for it); then every tile, cache or window, is
 //   copied HBM -> LDS with direct 16-byte loads through a ring.  The
 //   tiles that reach L are masked; in the tile that runs past T the keys >= T
 //   read the sequence's last page again and their V values are zeroed before
@@ -38,10 +39,11 @@
 //     than CUs (products of one under the softmax of the other), stops at the
 //     last key its rows see, and merges without a count-in when it holds the
 //     whole item.  One workgroup per chunk, one per CU, every row tile
-//     appending the window and running to its end (before -> after):
-//     8832 prefill rows 855 -> 107 us per layer, 32 sequences of 1k-4k with
-//     128 rows each 132 -> 78, 8 of 1.1k-2.1k with 1088 rows each 205 -> 82,
-//     with 128 rows 29 -> 25, with 4 rows (AR) 22 -> 21;
+//     appending the window and running to its end (before -> after, appends
+//     and merges included, graph replays of the call with 16/4 heads of 96):
+//     8832 prefill rows 760 -> 104 us, 32 sequences of 1k-4k with 128 rows
+//     each 123 -> 59, 8 of 1.1k-2.1k with 1088 rows each 203 -> 92, with 128
+//     rows 24.2 -> 19.4, with 4 rows (AR) 20.3 -> 16.3;
 //   * balanced (chunk_keys == 0): the items' tiles are concatenated and every
 //     workgroup takes an equal contiguous share, so the grid finishes together
 //     whatever the length mix; only shares that split an item publish
@@ -1637,7 +1639,7 @@ __global__ void __launch_bounds__(NP * 128, 1) attn_bf16_pc_kernel(AttnParams p)
 // (a head-dim element of a page is 64 contiguous bytes of the pool: four
 // 16-byte loads per element and page); the waves' sums meet at the end.
 // Latency-bound at the sizes it serves (16 rows x 4 heads x 272 keys of 64:
-// 72 -> 14 us; with one element per load and one wave over the 256 keys
+// 72 -> 11.6 us; with one element per load and one wave over the 256 keys
 // before).
 // ---------------------------------------------------------------------------
 // (fp32 arrays need only the alignment of their elements: a tensor that

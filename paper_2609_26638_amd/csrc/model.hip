@@ -1257,10 +1257,10 @@ namespace dvs {
 // x 32 columns walks k in ascending order (a row's result does not depend on
 // the row count).  Bound by the latency of its loads at the sizes it serves:
 // the fragments of 64 k are read at once, the next 64 under their products
-// (16 rows x 256 columns, K = 256: 22.6 -> 7 us with one step of 8 k in
-// flight before), and each wave is a workgroup, on a CU of its own while there
-// are any.  Up to three weight matrices side by side (Wq|Wk|Wv, gate|up), each
-// of its own column count and output.
+// (16 rows, K = 256, 256 to 1024 columns: 22.9 us per launch with one step of
+// 8 k in flight, 8.4 now), and each wave is a workgroup, on a CU of its own
+// while there are any.  Up to three weight matrices side by side (Wq|Wk|Wv,
+// gate|up), each of its own column count and output.
 struct F32Segs {
   const float* W[3];
   float* C[3];
