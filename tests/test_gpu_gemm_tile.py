@@ -30,15 +30,16 @@ def _model(H, Hq, Hkv, D, ffn, V, S, nc, nm):
 
 
 def _shift(dm, shift):
-    """The GEMMs' weights start ``shift`` elements into another tensor."""
+    """Every weight starts ``shift`` elements into another tensor."""
     def moved(t):
         buf = torch.empty(t.numel() + shift, dtype=t.dtype, device="cuda")
         return buf[shift:].view(t.shape).copy_(t)
 
-    dm.lm_head = moved(dm.lm_head)
-    dm.desc.lm_head = dm.lm_head.data_ptr()
+    for n in ("embed", "g_final", "lm_head"):
+        setattr(dm, n, moved(getattr(dm, n)))
+        setattr(dm.desc, n, getattr(dm, n).data_ptr())
     for l, t in enumerate(dm.keep):
-        for n in ("wq", "wk", "wv", "wo", "w_gate", "w_up", "w_down"):
+        for n in t:
             t[n] = moved(t[n])
             setattr(dm.layers[l], n, t[n].data_ptr())
             assert t[n].data_ptr() % 16 == shift * 2 % 16
